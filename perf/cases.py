@@ -423,12 +423,12 @@ def fraction(corners, phi):
 def courant_step(mesh, F, co=0.5):
     """The step at which the largest cell Courant number (1/2) sum |F_f| dt / V
     is `co`."""
-    out = torch.zeros(mesh.n_cells, dtype=F8, device=DEV)
-    out.index_add_(0, mesh.owner.to(I8), F.abs())
-    out.index_add_(0, mesh.neighbour.to(I8), F[: mesh.neighbour.shape[0]].abs())
+    F = F.abs().cpu().numpy()
+    own, nei = mesh.owner.cpu().numpy(), mesh.neighbour.cpu().numpy()
+    out = np.bincount(own, F, mesh.n_cells) + np.bincount(nei, F[: nei.shape[0]], mesh.n_cells)
     p = mesh.points[mesh.corners if mesh.corners.shape[1] == 4 else mesh.corners[:, [0, 1, 2, 4]]]
     V = torch.linalg.det(p[:, 1:] - p[:, :1]).abs() / (6.0 if mesh.corners.shape[1] == 4 else 1.0)
-    return co / float((0.5 * out / V).max())
+    return co / float((0.5 * out / V.cpu().numpy()).max())
 
 
 # ---------------------------------------------------------------------------
