@@ -343,7 +343,7 @@ class Field:
             return 0.25 * (torch.linalg.cross(self.w.expand_as(p), p + q) * (q - p)).sum(1)
         if self.kind == "rotation":
             a, b = p - self.o, q - self.o
-            return -((q - p) @ self.w) * ((a * a).sum(1) + (a * b).sum(1) + (b * b).sum(1)) / 6.0
+            return -((q - p) * self.w).sum(1) * ((a * a).sum(1) + (a * b).sum(1) + (b * b).sum(1)) / 6.0
         t, w = np.polynomial.legendre.leggauss(6)
         s, d = _sinpi, q - p
         acc = torch.zeros(p.shape[0], dtype=F8, device=DEV)
