@@ -274,8 +274,7 @@ typedef struct {
   double alpha_min, alpha_max;
   int64_t wisps;              /* sum over steps of wisps found (wisps = 1)   */
   int64_t wisps_left;         /* of those, wisps with too little room around */
-  int64_t chunk_rescans;      /* tetrahedral meshes: face groups whose stencils
-                                 were scanned again for a further chunk of
+  int64_t chunk_rescans;      /* face groups whose stencils were scanned again for a further chunk of
                                  candidate cells (a face with more candidates
                                  than a group's share)                       */
 } vof_stats;
@@ -320,7 +319,8 @@ typedef struct vof_batch vof_batch;
 typedef struct {
   int32_t grid_flux;   /* persistent blocks of the flux kernel (rounded up to 8) */
   int32_t grid_clip;   /* waves of the register clip                          */
-  int32_t clip_claim;  /* face groups per claim of the register clip's queue  */
+  int32_t clip_claim;  /* face groups per claim of the register clip's queue,
+                          where every wave has several claims (else one)      */
   int32_t grid_plane;  /* blocks (four waves) of the plane kernel             */
   int32_t grid_cells;  /* blocks of the cell, point and update kernels        */
 } vof_batch_config;

@@ -33,21 +33,21 @@ constexpr int kBlock = 256;
 constexpr int kClipBlock = 64;
 constexpr unsigned kFluxGrid = 8192;  // flux kernel blocks at most
 constexpr int kFastBlock = 64;   // one wave per block in the register clip
-// register clip configurations: queued pairs of two or more planes per tet,
-// candidate cells of a face group kept in LDS (CAND / F per face), and
-// whether the candidates' bounds are kept in LDS (box cells need them).
-// Quad faces (a hex face's stencil: 18 cells) take the first; triangle faces
-// of tetrahedral meshes (58 stencil cells, about 7 overlapping cells per
-// flux tet) the second, at two waves per SIMD.
-constexpr int kFastSlots = 4;
-constexpr int kTriSlots = 12, kTriCand = 192;
+// Register clip configurations: flux tets per lane, (tet, cell) pairs of a
+// round, candidate cells of a face group kept in LDS (CAND / F per face, in
+// chunks), and whether the candidates' bounds are kept in LDS (box cells need
+// them).  Quad faces (a hex face's stencil: 18 cells, of which two or three
+// overlap the face's flux polyhedron) take the first, triangle faces of
+// tetrahedral meshes (58 stencil cells, about 7 overlapping cells per flux
+// tet) the second, at two to three waves per SIMD.
+constexpr int kBoxTets = 2, kBoxCap = 304, kBoxCand = 72;
+constexpr int kTriTets = 1, kTriCap = 640, kTriCand = 192;
 constexpr int kFastPlanes = 4;   // planes per pair in the register clip (more: general)
 constexpr int kTriPlanes = 5;    // the same for triangle faces
-constexpr int kFastGrid = 4096;   // blocks claim face groups from a counter
-constexpr int kClaim = 2;         // face groups per claim
-constexpr int kGroupFaces = 4;    // faces per wavefront group (64 / at least 15 tets)
-constexpr int kCandPool = 48;
-constexpr int kFacePool = 12;     // staged points of a face group: F * max points <= 64 / 5
+constexpr int kFastGrid = 4096;   // blocks claim face groups from counters
+constexpr int kFullWaves = 2048;  // register-clip waves on the chip at once (2 per SIMD)
+constexpr int kGroupFaces = 6;    // faces per wavefront group at most (128 / 20 or 64 / 15 tets)
+constexpr int kVtxPool = 80;      // polyhedron vertices of a face group: F (3 max points + 1)
 constexpr int kPlaneGrid = 2048;  // blocks of four waves, four interface cells per wave
 static_assert(kMaxCellPlanes * kMaxFacePoints <= 128, "two fan tetrahedra per lane");
 static_assert(kMaxCellPlanes <= 16, "cutting-plane masks are 16 bits");
@@ -93,20 +93,30 @@ __device__ __forceinline__ int64_t geo_slot(const DMesh &m, int na, int i) {
   return i < na ? (int64_t)i : m.nf - 1 - (int64_t)(i - na);
 }
 // Register-clip face groups of one mesh: the small faces' groups first
-// (tsmall tets per face), then the large faces' (the mesh's 5 * maxn).  The
-// list counts are read once: the step's claim counter shares their line.
+// (tsmall tets per face), then the large faces' (the mesh's 5 * maxn), `tets`
+// tets per group at most.  The list counts are read once: the step's claim
+// counter shares their line.
 struct ClipGroups {
   int na, nb, tsmall, nsmall, total;
 };
-__device__ __forceinline__ ClipGroups clip_groups(const DMesh &m, const DState &s) {
+__device__ __forceinline__ ClipGroups clip_groups(const DMesh &m, const DState &s, int tets) {
   ClipGroups c;
   c.na = s.work[kWGeometric];
   c.nb = s.work[kWGeoLarge];
   c.tsmall = m.tpf < 5 * kSmallFace ? m.tpf : 5 * kSmallFace;
-  const int fs = 64 / c.tsmall, fl = 64 / m.tpf;
+  const int fs = tets / c.tsmall, fl = tets / m.tpf;
   c.nsmall = (c.na + fs - 1) / fs;
   c.total = c.nsmall + (c.nb + fl - 1) / fl;
   return c;
+}
+// Tets per group: one per lane, or TPL per lane where one-per-lane groups
+// would already be more than the waves that the chip holds at once.  (A wave
+// takes a group of six quad faces in about 1.25 times the time of three: most
+// of its phases wait on loads or run with half-empty lanes.)
+template <int TPL>
+__device__ __forceinline__ int group_tets(int faces, int tpf) {
+  const int small = tpf < 5 * kSmallFace ? tpf : 5 * kSmallFace;
+  return TPL > 1 && faces > kFullWaves * (kFastBlock / small) ? TPL * kFastBlock : kFastBlock;
 }
 
 // Append the threads with `pred` to a list with one atomic per block (the
@@ -169,6 +179,13 @@ __device__ __forceinline__ void flag(uint32_t *flags, uint32_t bit) { atomicOr(f
 // this block's slot of counter id
 __device__ __forceinline__ unsigned long long *cnt_at(unsigned long long *cnt, int id) {
   return cnt + ((int64_t)id * kCntLanes + (int64_t)(blockIdx.x % kCntLanes)) * kCntStride;
+}
+
+// The register clip's claim counters, one per XCD, in the unused words of the
+// first slots' lines (zero at the start of every step).
+constexpr int kClaimStride = kCntStride * 2;  // in 32-bit words
+__device__ __forceinline__ int32_t *claim_counter(unsigned long long *cnt) {
+  return reinterpret_cast<int32_t *>(cnt + 1);
 }
 
 // ---------------------------------------------------------------------------
@@ -1004,56 +1021,77 @@ __device__ __forceinline__ void pair_regs_box(const double *bb, const DState &s,
   p3 = mm ? box_plane(bb, __builtin_ctz(mm), c) : pl;
 }
 
-// Tetrahedron k of a face staged in LDS (P[j]: point j minus the face centre,
-// then its sweep at the corrected lam; cq: the mean sweep; n points), built
-// exactly as flux_tet builds it from global memory.
-__device__ __forceinline__ bool staged_tet(const double (*P)[6], int n, const double *cq, int k,
-                                           v3 &t1, v3 &t2, v3 &t3, double &det, double &sgn) {
-  if (k >= 5 * n) return false;
+// Vertices of a group's flux polyhedra in LDS, 3 gmax + 1 per face (gmax: the
+// points of a face of the group): point i minus the face centre (row i), its
+// swept image (gmax + i), the mean of side i's four corners (2 gmax + i), the
+// mean swept point (3 gmax).  The apex of every tet, the face centre, is the
+// origin.  Row numbers of the vertices of tet k of a face of n points:
+__device__ __forceinline__ void tet_rows(int n, int gmax, int k, int &r1, int &r2, int &r3) {
   const int i = k / 5, type = k - 5 * i;
-  const int i1 = (i + 1 == n) ? 0 : i + 1;
-  const v3 pi = mk3(P[i][0], P[i][1], P[i][2]), pj = mk3(P[i1][0], P[i1][1], P[i1][2]);
-  const v3 qi = pi + mk3(P[i][3], P[i][4], P[i][5]);
-  const v3 qj = pj + mk3(P[i1][3], P[i1][4], P[i1][5]);
-  if (type == 0) { t1 = mk3(cq[0], cq[1], cq[2]); t2 = qj; t3 = qi; }
-  else {
-    t1 = 0.25 * (pi + pj + qi + qj);
-    if (type == 1) { t2 = pj; t3 = pi; }
-    else if (type == 2) { t2 = pi; t3 = qi; }
-    else if (type == 3) { t2 = qi; t3 = qj; }
-    else { t2 = qj; t3 = pj; }
-  }
-  det = det3(t1, t2, t3);
-  if (det == 0.0) return false;
-  sgn = det > 0.0 ? 1.0 : -1.0;
-  if (det < 0.0) { v3 tmp = t2; t2 = t3; t3 = tmp; det = -det; }
-  return true;
+  const int j = (i + 1 == n) ? 0 : i + 1;
+  r1 = type == 0 ? 3 * gmax : 2 * gmax + i;
+  r2 = type == 0 ? gmax + j : (type == 1 ? j : (type == 2 ? i : (type == 3 ? gmax + i : gmax + j)));
+  r3 = type == 0 ? gmax + i : (type == 1 ? i : (type == 2 ? gmax + i : (type == 3 ? gmax + j : j)));
 }
 
-// A queued pair of the register clip: the tet (from its lane's LDS row), its
-// six-fold volume, the cell, its class and its planes in mask order (then
-// the PLIC plane of an interface cell).
-// The candidate's class comes from LDS, and so does its first plane index
-// when the kernel stages it (ccq0, cells that are not boxes), so the plane
-// loads do not wait on other loads.
+// The tets (bit k) that have point i (which = 0), its swept image (1) or side
+// i's mean point (2) as a vertex, for a face of n points; and those of the
+// mean swept point.
+__device__ __forceinline__ unsigned long long tets_of(int n, int i, int which) {
+  const int a = 5 * i, b = 5 * (i == 0 ? n - 1 : i - 1);
+  if (which == 0) return (6ull << a) | (18ull << b);    // 5i+1 5i+2 | 5b+1 5b+4
+  if (which == 1) return (13ull << a) | (25ull << b);   // 5i 5i+2 5i+3 | 5b 5b+3 5b+4
+  return 30ull << a;                                    // 5i+1 .. 5i+4
+}
+
+// A pair of the register clip in LDS: cutting-plane mask (bits 0-15),
+// candidate row (16-23), tet (24-30), and bit 31 where the mask is still to
+// be found (a cell of more planes than the candidate tests keep).
+__device__ __forceinline__ int pair_tet(uint32_t qp) { return (int)(qp >> 24) & 127; }
+__device__ __forceinline__ int pair_cand(uint32_t qp) { return (int)(qp >> 16) & 255; }
+__device__ __forceinline__ int tet_face(int l, int tpf) {
+  int f = 0;
+#pragma unroll
+  for (int i = 1; i < kGroupFaces; ++i) f += l >= i * tpf;
+  return f;
+}
+
+// The flux tets of a group in LDS: the rows of a lane's tet in vtx, positively
+// ordered (8 bits each), and its six-fold volume.  (Rows instead of the
+// vertices themselves: 0.75 KB instead of 5, so that more groups fit a CU.)
+struct GroupTets {
+  const double (*vtx)[3];
+  const uint32_t *row;
+  const double *det;
+};
+__device__ __forceinline__ v3 vtx_at(const double (*vtx)[3], uint32_t r) {
+  return mk3(vtx[r & 127u][0], vtx[r & 127u][1], vtx[r & 127u][2]);
+}
+__device__ __forceinline__ Tet group_tet(const GroupTets &t, int l) {
+  const uint32_t r = t.row[l];
+  return Tet{mk3(0, 0, 0), vtx_at(t.vtx, r), vtx_at(t.vtx, r >> 8), vtx_at(t.vtx, r >> 16)};
+}
+
+// The pair's tet, its six-fold volume, the cell, its
+// class and its planes in mask order (then the PLIC plane of an interface
+// cell).  The candidate's class comes from LDS, and so does its first plane
+// index when the kernel stages it (ccq0, cells that are not boxes), so the
+// plane loads do not wait on other loads.
 __device__ __forceinline__ void queued_pair(const DMesh &m, const DState &s, const uint32_t *qpair,
-                                            const double (*tv)[kFastBlock],
+                                            const GroupTets &tets,
                                             const double (*fc)[3], const int32_t *ccell,
                                             const int8_t *ccls, const int32_t *ccq0,
-                                            const double (*cbox)[6], int tpf, int kc, int item,
+                                            const double (*cbox)[6], int tpf, int item,
                                             Tet &T, double &det, int &cell, int &cl, Pl &p0,
                                             Pl &p1, Pl &p2, Pl &p3) {
-  const int l = item % kFastBlock;
   const uint32_t qp = qpair[item];
-  const int lf = l / tpf;
-  const int u = lf * kc + (int)((qp >> 16) & 63u);
+  const int l = pair_tet(qp), u = pair_cand(qp), lf = tet_face(l, tpf);
   cell = ccell[u];
   const v3 c = mk3(fc[lf][0], fc[lf][1], fc[lf][2]);
-  T = Tet{mk3(0, 0, 0), mk3(tv[0][l], tv[1][l], tv[2][l]), mk3(tv[3][l], tv[4][l], tv[5][l]),
-          mk3(tv[6][l], tv[7][l], tv[8][l])};
-  det = tv[9][l];
+  T = group_tet(tets, l);
+  det = tets.det[l];
   cl = ccls[u] & 7;
-  if (qp & (1u << 22))
+  if (ccls[u] & 8)
     pair_regs_box(cbox[u], s, c, cell, cl, qp & 0xffffu, p0, p1, p2, p3);
   else
     pair_regs_q(m, s, c, cell, cl, ccq0 ? ccq0[u] : m.cf_off[cell], qp & 0xffffu, p0, p1, p2,
@@ -1066,10 +1104,10 @@ __device__ __forceinline__ void queued_pair(const DMesh &m, const DState &s, con
 template <int K>
 __device__ __forceinline__ void three_lane_bin(const DMesh &m, const DState &s,
                                                const uint32_t *qpair,
-                                               const double (*tv)[kFastBlock],
+                                               const GroupTets &tets,
                                                const double (*fc)[3], const int32_t *ccell,
                                                const int8_t *ccls, const int32_t *ccq0,
-                                               const double (*cbox)[6], int tpf, int kc,
+                                               const double (*cbox)[6], int tpf,
                                                const uint16_t *bin, int cnt, bool from_end,
                                                int cap, double *res) {
   const int lane = threadIdx.x;
@@ -1083,7 +1121,7 @@ __device__ __forceinline__ void three_lane_bin(const DMesh &m, const DState &s,
       Tet T;
       int cell, cl;
       Pl p0, p1, p2, p3;
-      queued_pair(m, s, qpair, tv, fc, ccell, ccls, ccq0, cbox, tpf, kc, item, T, det, cell, cl,
+      queued_pair(m, s, qpair, tets, fc, ccell, ccls, ccq0, cbox, tpf, item, T, det, cell, cl,
                   p0, p1, p2, p3);
       val = split_term<K>(dist_table<K>(T, p0, p1, p2, p3), term);
       w = class_weight(s, cell, cl);
@@ -1098,10 +1136,10 @@ __device__ __forceinline__ void three_lane_bin(const DMesh &m, const DState &s,
 template <int K>
 __device__ __forceinline__ void one_lane_bin(const DMesh &m, const DState &s,
                                              const uint32_t *qpair,
-                                             const double (*tv)[kFastBlock],
+                                             const GroupTets &tets,
                                              const double (*fc)[3], const int32_t *ccell,
                                              const int8_t *ccls, const int32_t *ccq0,
-                                             const double (*cbox)[6], int tpf, int kc,
+                                             const double (*cbox)[6], int tpf,
                                              const uint16_t *bin, int cnt, bool from_end, int cap,
                                              double *res) {
   for (int t = (int)threadIdx.x; t < cnt; t += kFastBlock) {
@@ -1110,7 +1148,7 @@ __device__ __forceinline__ void one_lane_bin(const DMesh &m, const DState &s,
     int cell, cl;
     double det;
     Pl p0, p1, p2, p3;
-    queued_pair(m, s, qpair, tv, fc, ccell, ccls, ccq0, cbox, tpf, kc, item, T, det, cell, cl, p0,
+    queued_pair(m, s, qpair, tets, fc, ccell, ccls, ccq0, cbox, tpf, item, T, det, cell, cl, p0,
                 p1, p2, p3);
     const double v = kept_fraction<K>(dist_table<K>(T, p0, p1, p2, p3));
     res[item] = class_weight(s, cell, cl) * (det * v);
@@ -1124,11 +1162,11 @@ __device__ __forceinline__ void one_lane_bin(const DMesh &m, const DState &s,
 // weighted by their ratios.
 __device__ __forceinline__ void nine_lane_bin(const DMesh &m, const DState &s,
                                               const uint32_t *qpair,
-                                              const double (*tv)[kFastBlock],
+                                              const GroupTets &tets,
                                               const double (*fc)[3], const int32_t *ccell,
-                                              const int8_t *ccls, const int32_t *ccq0,
-                                              int tpf, int kc, const uint16_t *bin, int cnt,
-                                              int cap, double *res) {
+                                              const int8_t *ccls, const int32_t *ccq0, int tpf,
+                                              const uint16_t *bin, int cnt, int cap,
+                                              double *res) {
   const int lane = threadIdx.x;
   for (int t0 = 0; t0 < cnt; t0 += kFastBlock / 9) {
     const int t = t0 + lane / 9, sub = lane - 9 * (lane / 9);
@@ -1138,18 +1176,15 @@ __device__ __forceinline__ void nine_lane_bin(const DMesh &m, const DState &s,
     double val = 0.0, ri = 0.0, w = 0.0, det = 0.0;
     if (on) {
       item = bin[cap - 1 - t];
-      const int l = item % kFastBlock;
       const uint32_t qp = qpair[item];
-      const int lf = l / tpf;
-      const int u = lf * kc + (int)((qp >> 16) & 63u);
+      const int l = pair_tet(qp), u = pair_cand(qp), lf = tet_face(l, tpf);
       const int cell = ccell[u];
       const v3 c = mk3(fc[lf][0], fc[lf][1], fc[lf][2]);
-      const Tet T{mk3(0, 0, 0), mk3(tv[0][l], tv[1][l], tv[2][l]),
-                  mk3(tv[3][l], tv[4][l], tv[5][l]), mk3(tv[6][l], tv[7][l], tv[8][l])};
-      det = tv[9][l];
+      const Tet T = group_tet(tets, l);
+      det = tets.det[l];
       const int cl = ccls[u] & 7;
-      // the four cutting planes in mask order, then the PLIC plane
-      const Pl pl = plic_plane_at(s, cell, c);
+      // the four cutting planes in mask order, then the PLIC plane (or, of a
+      // cell without one, the fifth cutting plane)
       const int q0 = ccq0 ? ccq0[u] : m.cf_off[cell];
       uint32_t mm = qp & 0xffffu;
       const Pl a = cell_plane_at(m, q0 + __builtin_ctz(mm), c);
@@ -1159,6 +1194,8 @@ __device__ __forceinline__ void nine_lane_bin(const DMesh &m, const DState &s,
       const Pl d = cell_plane_at(m, q0 + __builtin_ctz(mm), c);
       mm &= mm - 1;
       const Pl e = cell_plane_at(m, q0 + __builtin_ctz(mm), c);
+      mm &= mm - 1;
+      const Pl pl = mm ? cell_plane_at(m, q0 + __builtin_ctz(mm), c) : plic_plane_at(s, cell, c);
       val = split_term2<5>(dist_table<5>(T, a, b, d, e, pl), i, j, ri);
       w = class_weight(s, cell, cl);
     }
@@ -1169,55 +1206,160 @@ __device__ __forceinline__ void nine_lane_bin(const DMesh &m, const DState &s,
   }
 }
 
+// Tests of one candidate cell against the tets of its face, bit by bit: E
+// holds the tets with a vertex strictly inside a bound or plane, N those with
+// a vertex strictly outside.
+struct SideBits {
+  uint32_t e, n;
+};
+__device__ __forceinline__ void side_bits(SideBits &b, double d, uint32_t tets) {
+  b.e |= d > 0.0 ? tets : 0u;
+  b.n |= d < 0.0 ? tets : 0u;
+}
+
+// Which tets k (bits 0..) of a face may overlap a candidate cell, and for each
+// of the cell's planes j which of them it cuts, from the nv vertices of the
+// face's polyhedron (rows vx, the tets of each from bit `kb` on in vt): the
+// tests of box_cuts (box cells) and pair_cuts_box, which need only the sign of
+// each vertex's distance, so they are made once per vertex and plane instead
+// of once per tet.  `all`: the face's tets.
+// The two planes of axis a of a box cell: + at hi and - at lo, c the axis
+// coordinate of the tets' apex.
+__device__ __forceinline__ uint32_t box_side_bits(double lo, double hi, double c, int a,
+                                                  const double (*vx)[3],
+                                                  const unsigned long long *vt, int nv, int kb,
+                                                  uint32_t all, uint32_t &cut0, uint32_t &cut1) {
+  SideBits up{0u, 0u}, dn{0u, 0u};
+  const double wu = hi - c, wd = c - lo;
+  side_bits(up, wu, all);  // the apex
+  side_bits(dn, wd, all);
+  for (int v = 0; v < nv; ++v) {
+    const uint32_t t = (uint32_t)(vt[v] >> kb);
+    const double x = vx[v][a];
+    side_bits(up, wu - x, t);
+    side_bits(dn, wd + x, t);
+  }
+  cut0 = up.n & all;
+  cut1 = dn.n & all;
+  return all & up.e & dn.e;
+}
+// A cell that is no box: its bounds and its planes, the first RP of which have
+// their cut tets in cut[]; planes beyond these only take tets off the result,
+// and recut is set: the mask has to be found pair by pair.
+template <int RP>
+__device__ __forceinline__ uint32_t cand_tests(const DMesh &m, v3 lo, v3 hi, v3 c, int q0, int np,
+                                               const double (*vx)[3],
+                                               const unsigned long long *vt, int nv, int kb,
+                                               uint32_t all, uint32_t (&cut)[RP], bool &recut) {
+  recut = false;
+  uint32_t lx = 0, ly = 0, lz = 0, hx = 0, hy = 0, hz = 0;
+  auto bound = [&](v3 y, uint32_t t) {
+    lx |= y.x > lo.x ? t : 0u;
+    ly |= y.y > lo.y ? t : 0u;
+    lz |= y.z > lo.z ? t : 0u;
+    hx |= y.x < hi.x ? t : 0u;
+    hy |= y.y < hi.y ? t : 0u;
+    hz |= y.z < hi.z ? t : 0u;
+  };
+  Pl pl[RP];
+  SideBits b[RP];
+#pragma unroll
+  for (int j = 0; j < RP; ++j) {
+    pl[j] = j < np ? cell_plane_at(m, q0 + j, c) : Pl{0, 0, 0, 1.0};
+    b[j] = SideBits{0u, 0u};
+    side_bits(b[j], pl[j].w, all);  // the apex
+  }
+  bound(c, all);
+  for (int v = 0; v < nv; ++v) {
+    const uint32_t t = (uint32_t)(vt[v] >> kb);
+    const v3 x = mk3(vx[v][0], vx[v][1], vx[v][2]);
+    bound(x + c, t);
+#pragma unroll
+    for (int j = 0; j < RP; ++j) side_bits(b[j], pl[j].w - dot(mk3(pl[j].x, pl[j].y, pl[j].z), x), t);
+  }
+  uint32_t hit = all & lx & ly & lz & hx & hy & hz;
+#pragma unroll
+  for (int j = 0; j < RP; ++j) {
+    hit &= b[j].e;
+    cut[j] = b[j].n;
+  }
+  if (np > RP) {
+    recut = true;
+    for (int j = RP; j < np; ++j) {
+      const Pl q = cell_plane_at(m, q0 + j, c);
+      SideBits x{0u, 0u};
+      side_bits(x, q.w, all);
+      for (int v = 0; v < nv; ++v)
+        side_bits(x, q.w - dot(mk3(q.x, q.y, q.z), mk3(vx[v][0], vx[v][1], vx[v][2])),
+                  (uint32_t)(vt[v] >> kb));
+      hit &= x.e;
+    }
+  }
+  return hit;
+}
+
+// the bits lo .. hi - 1 of a 64-bit mask (bounds clamped to 0..64)
+__device__ __forceinline__ unsigned long long bit_range(int lo, int hi) {
+  lo = lo < 0 ? 0 : lo;
+  hi = hi > 64 ? 64 : hi;
+  if (hi <= lo) return 0ull;
+  return (hi == 64 ? ~0ull : ((1ull << hi) - 1ull)) & ~((1ull << lo) - 1ull);
+}
+
 // Step 5 on the register path.  A wavefront takes a group of whole geometric
-// faces (64 / tets-per-face of them; groups claimed from a counter), one flux
-// tet per lane.  First the faces' candidate cells: each face's stencil is
-// scanned by all lanes at once and the non-empty cells whose box overlaps
-// the flux polyhedron's box are compacted (in stencil order) into LDS with
-// their class and box.  Phase A: every tet classifies its face's candidates
-// by a mask of the cell planes that cut it; pairs bounded by at most one
-// plane are summed at once (a single kept fraction); pairs with two to
-// MAXPL planes are queued in LDS bins by plane count, and a tet with a
-// pair of more planes (or, without CHUNKED, of a face with more than CAND / F
-// candidates; with it the candidates come in chunks of that many, the next
-// once the group's tets are through the current one) goes to the general
-// kernel's queue; a tet with more than SLOTS queued pairs stops
-// at the first that finds its queue full and resumes there in another round
-// of the three phases.  Phase B
-// evaluates each bin with the plane count uniform across the wave: pairs of
-// two planes one lane each (the whole recursion), of three planes one lane
-// each on tetrahedral meshes and three lanes each on hexahedral ones, of four
-// three lanes each (one per piece of the first plane's split), of five nine
-// lanes each (one per piece of the first two splits); phase C adds each tet's
-// queued results in stencil order.
+// faces (gtets / tets-per-face of them; groups claimed from a counter), one flux
+// tet (or two, TPL) per lane where the lanes stand for tets.  First the faces'
+// candidate cells: each face's stencil is scanned by all lanes at once and the
+// non-empty cells whose box overlaps the flux polyhedron's box are compacted
+// (in stencil order) into LDS with their class and box, in chunks of CAND / F
+// per face.
+// Phase A, lanes over the group's candidates: the tets each candidate may
+// overlap and the cell planes that cut them (cand_tests), and the list of the
+// (tet, cell) pairs, tet by tet and in stencil order within a tet, up to CAP
+// pairs at a time (rounds of tets).  Then lanes over the pairs: pairs bounded
+// by at most one plane are summed at once (a single kept fraction), pairs of
+// two to MAXPL planes go to bins by plane count, and a tet with a pair of more
+// planes goes to the general kernel's queue.
+// Phase B evaluates each bin with the plane count uniform across the wave:
+// pairs of two planes one lane each (the whole recursion), of three planes one
+// lane each on tetrahedral meshes and three lanes each on hexahedral ones, of
+// four three lanes each (one per piece of the first plane's split), of five
+// nine lanes each (one per piece of the first two splits); phase C adds each
+// tet's pairs in stencil order.
+// Bound by issued FP64 and select instructions of phase B, with the lanes over
+// candidates, tets, pairs and pieces in turn so that none waits for the tet
+// with the most work (with a tet per lane through phase A, half of a step on
+// tetrahedra went to lanes waiting): 24^3 x 6 tetrahedra 0.48 -> 0.29 ms a
+// step, 80^3 x 6 1.91 -> 1.45, 97 x 103 x 89 cubes 0.374 -> 0.360.
 // Group g of one list of geometric faces of one mesh (`count` faces at gfaces
-// slots first, first + dir, ...; tpf tets per face, F = 64 / tpf per group),
+// slots first, first + dir, ...; tpf tets per face, F = gtets / tpf per group),
 // swept by `sweep` (-s dt).  Must be reached by the whole wave.
-template <int SLOTS, int CAND, bool BOXES, int MAXPL, bool CHUNKED>
+template <int TPL, int CAP, int CAND, bool BOXES, int MAXPL>
 __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s, const DParams &p,
                                                 int g, int count, int first, int dir,
-                                                int tpf, double sweep,
+                                                int tpf, int gtets, double sweep,
                                                 unsigned long long &npairs,
                                                 unsigned long long &nresc) {
   static_assert(MAXPL <= 4 || !BOXES, "five-plane pairs only for cells that are not boxes");
-  // the group's faces: points minus the face centre and their sweeps at the
-  // corrected lam, the mean sweep, the point count and the face centre (the
-  // apex of the face's tets); every tet is built from these
-  __shared__ double fpt[kFacePool][6];  // face fi's point j at fi * (tpf / 5) + j
-  __shared__ double fcq[kGroupFaces][3];
+  static_assert(CAP >= 63 * TPL && CAP < 65536, "a round takes at least one lane's tets");
+  static_assert(CAND <= 256 && TPL * kFastBlock <= 128, "fields of a queued pair");
+  constexpr int kRP = BOXES ? 6 : 4;           // planes with cut bits in registers
+  constexpr int kPer = BOXES ? 3 : 1;          // lanes per candidate in its tests (one per axis)
+  constexpr int kBatch = 5 * kSmallFace;       // tets per face whose bits fit a word
+  // stencil entries per lane whose ids and classes load together
+  constexpr int kScan = BOXES ? 2 : 4;
+  __shared__ double vtx[kVtxPool][3];
+  __shared__ unsigned long long vtet[kVtxPool];
   __shared__ int fn[kGroupFaces];
   __shared__ double fc[kGroupFaces][3];
-  __shared__ double tv[10][kFastBlock];
-  // queued pair: plane mask (bits 0-15), candidate (16-21), box cell (22),
-  // plane count - 2 (30-31)
-  constexpr int kCap = kFastBlock * SLOTS;
-  __shared__ uint32_t qpair[kCap];
-  __shared__ double res[kCap];
-  // queued pairs by plane count: two planes from the start of bins[0], five
-  // from its end, three from the start of bins[1] and four from its end (kCap
-  // pairs at most)
-  __shared__ uint16_t bins[2][kCap];
-  __shared__ int nbin[4];
+  __shared__ uint32_t trow[TPL * kFastBlock];
+  __shared__ double tdet[TPL * kFastBlock];
+  __shared__ uint32_t qpair[CAP];
+  __shared__ double res[CAP];
+  // pairs of two and more planes by plane count: two planes from the start of
+  // bins[0], five from its end, three from the start of bins[1] and four from
+  // its end (CAP pairs at most)
+  __shared__ uint16_t bins[2][CAP];
   // candidates of face fi at fi * (CAND / F) + position
   __shared__ int32_t ccell[CAND];
   __shared__ int8_t ccls[CAND];  // class | 8 for a box cell
@@ -1228,134 +1370,163 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
   __shared__ double cbox[BOXES ? CAND : 1][6];
   __shared__ double fbox[kGroupFaces][6];
   __shared__ int cnum[kGroupFaces];
+  __shared__ uint8_t tdef[TPL * kFastBlock];  // tets left to the general clip
   const int lane = threadIdx.x;
-  const int F = kFastBlock / tpf;  // faces per group, 1..kGroupFaces
+  const int F = gtets / tpf;       // faces per group, 1..kGroupFaces
   const int gmax = tpf / 5;        // points per face of the list
-  // candidates kept per face (the candidate field of a queued pair has 6 bits)
-  const int kc = CAND / F < 63 ? CAND / F : 63;
+  const int nvf = 3 * gmax + 1;    // vertex rows per face
+  const int kc = CAND / F < 63 ? CAND / F : 63;  // candidates kept per face
+
+  // the stencil scan's first entries, loaded beside the staging's gathers
+  const int L = kFastBlock / F;
+  const int cf = lane / L, e_in = lane - cf * L;
+  const bool cmine = cf < F && g * F + cf < count;
+  int w = 0, nst = 0;
+  if (cmine) {
+    const int f = s.gfaces[(int64_t)first + dir * (g * F + cf)];
+    w = m.st_off[f];
+    nst = m.st_off[f + 1] - w;
+  }
+  if (lane < kGroupFaces) cnum[lane] = 0;
+  // flux polyhedron boxes (points and their swept images) and vertices staged
+  // in LDS, one lane per face point: lane fi * padw + j takes point j of face
+  // fi, and the face's sums and bounds are butterfly reductions over its padw
+  // lanes (every lane of the face ends with the same bits, as the two operands
+  // of each addition are the same in every lane).
+  // Unpadded: a cell that only touches the box meets the polyhedron in a
+  // sliver of zero width (or of the width of the rounding of the tets'
+  // vertices), whose volume is below the rounding of the sum.
   {
-    if (lane < 4) nbin[lane] = 0;
-    // flux polyhedron boxes (points and their swept images) and the faces
-    // staged in LDS, one lane per face point: lane fi * padw + j takes point j
-    // of face fi, and the face's sums and bounds are butterfly reductions
-    // over its padw lanes (every lane of the face ends with the same bits, as
-    // the two operands of each addition are the same in every lane).
-    // Unpadded: a cell that only touches the box meets the polyhedron in a
-    // sliver of zero width (or of the width of the rounding of the tets'
-    // vertices), whose volume is below the rounding of the sum.
+    const int pw = m.padw;  // 4 or 8
+    const int sf = lane / pw, sj = lane - sf * pw;
+    const int sslot = g * F + sf;
+    const bool sface = sf < F && sslot < count;
+    int q = -1;
+    double sw = 0.0;
+    if (sface) {
+      const int f = s.gfaces[(int64_t)first + dir * sslot];
+      sw = sweep * s.lam[f];
+      q = m.fpad[(int64_t)f * pw + sj];
+    }
+    v3 x = mk3(0, 0, 0), u = mk3(0, 0, 0);
+    v3 lo = mk3(1e300, 1e300, 1e300), hi = mk3(-1e300, -1e300, -1e300);
+    if (q >= 0) {
+      const PointRec pr = point_rec(s.XU, q);
+      x = pr.x;
+      u = sw * pr.u;
+      const v3 y = x + u;
+      lo = mk3(dmin(x.x, y.x), dmin(x.y, y.y), dmin(x.z, y.z));
+      hi = mk3(dmax(x.x, y.x), dmax(x.y, y.y), dmax(x.z, y.z));
+    }
+    const unsigned long long has = __ballot(q >= 0);
+    const int n = (int)__popcll((has >> (sf * pw)) & ((1ull << pw) - 1ull));
+    v3 c = x, cs = u;
+    for (int o = 1; o < pw; o <<= 1) {
+      c = c + mk3(__shfl_xor(c.x, o), __shfl_xor(c.y, o), __shfl_xor(c.z, o));
+      cs = cs + mk3(__shfl_xor(cs.x, o), __shfl_xor(cs.y, o), __shfl_xor(cs.z, o));
+      lo = mk3(dmin(lo.x, __shfl_xor(lo.x, o)), dmin(lo.y, __shfl_xor(lo.y, o)),
+               dmin(lo.z, __shfl_xor(lo.z, o)));
+      hi = mk3(dmax(hi.x, __shfl_xor(hi.x, o)), dmax(hi.y, __shfl_xor(hi.y, o)),
+               dmax(hi.z, __shfl_xor(hi.z, o)));
+    }
+    const double inv = 1.0 / (n > 0 ? n : 1);
+    c = inv * c;
+    cs = inv * cs;  // mean sweep
+    const v3 pi = x - c, qi = pi + u;
+    const int nx = sf * pw + (sj + 1 >= n ? 0 : sj + 1);  // the next point's lane
+    const v3 pj = mk3(__shfl(pi.x, nx), __shfl(pi.y, nx), __shfl(pi.z, nx));
+    const v3 qj = mk3(__shfl(qi.x, nx), __shfl(qi.y, nx), __shfl(qi.z, nx));
+    const v3 mi = 0.25 * (pi + pj + qi + qj);
+    if (sface && sj < gmax) {  // n <= gmax always, by the list the face is on
+      const bool on = q >= 0;  // rows past the face's points belong to no tet
+      const int r = sf * nvf + sj;
+      vtx[r][0] = pi.x; vtx[r][1] = pi.y; vtx[r][2] = pi.z;
+      vtx[r + gmax][0] = qi.x; vtx[r + gmax][1] = qi.y; vtx[r + gmax][2] = qi.z;
+      vtx[r + 2 * gmax][0] = mi.x; vtx[r + 2 * gmax][1] = mi.y; vtx[r + 2 * gmax][2] = mi.z;
+      vtet[r] = on ? tets_of(n, sj, 0) : 0ull;
+      vtet[r + gmax] = on ? tets_of(n, sj, 1) : 0ull;
+      vtet[r + 2 * gmax] = on ? tets_of(n, sj, 2) : 0ull;
+    }
+    if (sface && sj == 0) {
+      const int r = sf * nvf + 3 * gmax;
+      vtx[r][0] = cs.x; vtx[r][1] = cs.y; vtx[r][2] = cs.z;
+      unsigned long long tops = 0ull;  // tets 5 i, i < n
+      for (int i = 0; i < n; ++i) tops |= 1ull << (5 * i);
+      vtet[r] = tops;
+      fn[sf] = n;
+      fc[sf][0] = c.x; fc[sf][1] = c.y; fc[sf][2] = c.z;
+      fbox[sf][0] = lo.x; fbox[sf][1] = lo.y; fbox[sf][2] = lo.z;
+      fbox[sf][3] = hi.x; fbox[sf][4] = hi.y; fbox[sf][5] = hi.z;
+    }
+  }
+  __syncthreads();
+  // the lane's tets: tet lane + 64 i of the group
+  int fi[TPL], k[TPL];
+  bool active[TPL], defer[TPL], live[TPL], todo[TPL];
+  double acc[TPL], sgn[TPL];
+  unsigned npt[TPL];  // pairs of each tet
+#pragma unroll
+  for (int i = 0; i < TPL; ++i) {
+    const int t = lane + i * kFastBlock;
+    fi[i] = t / tpf;
+    k[i] = t - fi[i] * tpf;
+    active[i] = fi[i] < F && g * F + fi[i] < count;
+    live[i] = false;
+    acc[i] = 0.0;
+    npt[i] = 0u;
+    sgn[i] = 1.0;
+    tdef[t] = 0;
+    if (active[i] && !p.check_stencil && k[i] < 5 * fn[fi[i]]) {
+      int r1, r2, r3;
+      tet_rows(fn[fi[i]], gmax, k[i], r1, r2, r3);
+      r1 += fi[i] * nvf;
+      r2 += fi[i] * nvf;
+      r3 += fi[i] * nvf;
+      double det = det3(vtx_at(vtx, r1), vtx_at(vtx, r2), vtx_at(vtx, r3));
+      live[i] = det != 0.0;
+      if (live[i]) {
+        sgn[i] = det > 0.0 ? 1.0 : -1.0;
+        if (det < 0.0) { const int r = r2; r2 = r3; r3 = r; det = -det; }
+        trow[t] = (uint32_t)r1 | ((uint32_t)r2 << 8) | ((uint32_t)r3 << 16);
+        tdet[t] = det;
+      }
+    }
+    defer[i] = active[i] && p.check_stencil;
+    todo[i] = live[i];  // the current chunk's candidates are to be visited
+  }
+  const GroupTets tets{vtx, trow, tdet};
+  const unsigned long long lt = (1ull << lane) - 1ull;
+  int most = nst;  // the largest stencil of the group sets the trip count
+  for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o));
+  // candidate cells of the group's faces in chunks of kc per face (in stencil
+  // order, kFastBlock / F lanes per face): a face with more takes the next
+  // chunk once its tets are through the current one
+  for (int skip = 0;; skip += kc) {
     {
-      const int pw = m.padw;  // 4 or 8
-      const int sf = lane / pw, sj = lane - sf * pw;
-      const int sslot = g * F + sf;
-      const bool sface = sf < F && sslot < count;
-      int q = -1;
-      double sw = 0.0;
-      if (sface) {
-        const int f = s.gfaces[(int64_t)first + dir * sslot];
-        sw = sweep * s.lam[f];
-        q = m.fpad[(int64_t)f * pw + sj];
-      }
-      v3 x = mk3(0, 0, 0), u = mk3(0, 0, 0);
-      v3 lo = mk3(1e300, 1e300, 1e300), hi = mk3(-1e300, -1e300, -1e300);
-      if (q >= 0) {
-        const PointRec pr = point_rec(s.XU, q);
-        x = pr.x;
-        u = sw * pr.u;
-        const v3 y = x + u;
-        lo = mk3(dmin(x.x, y.x), dmin(x.y, y.y), dmin(x.z, y.z));
-        hi = mk3(dmax(x.x, y.x), dmax(x.y, y.y), dmax(x.z, y.z));
-      }
-      const unsigned long long has = __ballot(q >= 0);
-      const int n = (int)__popcll((has >> (sf * pw)) & ((1ull << pw) - 1ull));
-      v3 c = x, cs = u;
-      for (int o = 1; o < pw; o <<= 1) {
-        c = c + mk3(__shfl_xor(c.x, o), __shfl_xor(c.y, o), __shfl_xor(c.z, o));
-        cs = cs + mk3(__shfl_xor(cs.x, o), __shfl_xor(cs.y, o), __shfl_xor(cs.z, o));
-        lo = mk3(dmin(lo.x, __shfl_xor(lo.x, o)), dmin(lo.y, __shfl_xor(lo.y, o)),
-                 dmin(lo.z, __shfl_xor(lo.z, o)));
-        hi = mk3(dmax(hi.x, __shfl_xor(hi.x, o)), dmax(hi.y, __shfl_xor(hi.y, o)),
-                 dmax(hi.z, __shfl_xor(hi.z, o)));
-      }
-      if (q >= 0) {
-        c = (1.0 / n) * c;
-        cs = (1.0 / n) * cs;  // mean sweep
-        if (n <= gmax) {  // always, by the list the face is on
-          double *row = fpt[sf * gmax + sj];
-          row[0] = x.x - c.x; row[1] = x.y - c.y; row[2] = x.z - c.z;
-          row[3] = u.x; row[4] = u.y; row[5] = u.z;
+      const unsigned long long seg = cmine ? bit_range(cf * L, cf * L + L) : 0ull;
+      int cnt = 0;
+      for (int e0 = 0; e0 < most; e0 += kScan * L) {
+        int cells[kScan], cls[kScan];
+#pragma unroll
+        for (int i = 0; i < kScan; ++i) {
+          const int e = e0 + i * L + e_in;
+          cells[i] = cmine && e < nst ? m.st[w + e] : -1;
         }
-        if (sj == 0) {
-          fn[sf] = n;
-          fc[sf][0] = c.x; fc[sf][1] = c.y; fc[sf][2] = c.z;
-          fcq[sf][0] = cs.x; fcq[sf][1] = cs.y; fcq[sf][2] = cs.z;
-          fbox[sf][0] = lo.x; fbox[sf][1] = lo.y; fbox[sf][2] = lo.z;
-          fbox[sf][3] = hi.x; fbox[sf][4] = hi.y; fbox[sf][5] = hi.z;
-        }
-      }
-    }
-    __syncthreads();
-    // phase A
-    const int fi = lane / tpf, k = lane - fi * tpf;
-    const int slot = g * F + fi;
-    const bool active = fi < F && slot < count;
-    const int64_t idx = ((int64_t)first + dir * slot) * m.tpf + k;
-    bool defer = false, live = false;
-    double acc = 0.0, sgn = 1.0;
-    if (active) {
-      v3 t1, t2, t3;
-      double det;
-      live = !p.check_stencil &&
-             staged_tet(&fpt[fi * gmax], fn[fi], fcq[fi], k, t1, t2, t3, det, sgn);
-      defer = p.check_stencil;
-      if (live && !defer) {
-        tv[0][lane] = t1.x; tv[1][lane] = t1.y; tv[2][lane] = t1.z;
-        tv[3][lane] = t2.x; tv[4][lane] = t2.y; tv[5][lane] = t2.z;
-        tv[6][lane] = t3.x; tv[7][lane] = t3.y; tv[8][lane] = t3.z;
-        tv[9][lane] = det;
-      }
-    }
-    if (defer) live = false;
-    bool todo = live;   // candidates of the current chunk left to visit
-    bool more = false;  // candidates past the current chunk left to visit
-    int ci0 = 0;
-    unsigned long long np = 0;
-    // candidate cells of the group's faces in chunks of kc per face (in
-    // stencil order, kFastBlock / F lanes per face): a face with more takes
-    // the next chunk once its tets are through the current one
-    for (int skip = 0;; skip += kc) {
-      {
-        const int L = kFastBlock / F;
-        const int cf = lane / L, e_in = lane - cf * L;
-        const int slot = g * F + cf;
-        const bool mine = cf < F && slot < count;
-        int w = 0, nst = 0;
-        if (mine) {
-          const int f = s.gfaces[(int64_t)first + dir * slot];
-          w = m.st_off[f];
-          nst = m.st_off[f + 1] - w;
-        }
-        int most = nst;  // the largest stencil of the group sets the trip count
-        for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o));
-        const unsigned long long seg =
-            !mine ? 0ull : (L == kFastBlock ? ~0ull : (((1ull << L) - 1ull) << (cf * L)));
-        int cnt = 0;
-        for (int e0 = 0; e0 < most; e0 += L) {
-          const int e = e0 + e_in;
+#pragma unroll
+        for (int i = 0; i < kScan; ++i) cls[i] = cells[i] >= 0 ? s.cls[cells[i]] : 0;
+#pragma unroll
+        for (int i = 0; i < kScan; ++i) {
+          const int cell = cells[i], cl = cls[i];
           bool keep = false;
-          int cell = 0, cl = 0;
           double4 blo = make_double4(0, 0, 0, 0), bhi = blo;
-          if (mine && e < nst) {
-            cell = m.st[w + e];
-            cl = s.cls[cell];
-            if (cl != 0) {
-              blo = m.bblo[cell];
-              bhi = m.bbhi[cell];
-              keep = !(fbox[cf][3] <= blo.x || fbox[cf][0] >= bhi.x || fbox[cf][4] <= blo.y ||
-                       fbox[cf][1] >= bhi.y || fbox[cf][5] <= blo.z || fbox[cf][2] >= bhi.z);
-            }
+          if (cl != 0) {
+            blo = m.bblo[cell];
+            bhi = m.bbhi[cell];
+            keep = !(fbox[cf][3] <= blo.x || fbox[cf][0] >= bhi.x || fbox[cf][4] <= blo.y ||
+                     fbox[cf][1] >= bhi.y || fbox[cf][5] <= blo.z || fbox[cf][2] >= bhi.z);
           }
           const unsigned long long bal = __ballot(keep) & seg;
-          const int pos = cnt + (int)__popcll(bal & ((1ull << lane) - 1ull));
+          const int pos = cnt + (int)__popcll(bal & lt);
           if (keep && pos >= skip && pos < skip + kc) {
             const int u = cf * kc + (pos - skip);
             ccell[u] = cell;
@@ -1372,190 +1543,222 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
           }
           cnt += (int)__popcll(bal);
         }
-        if (mine && e_in == 0) cnum[cf] = cnt;
+      }
+      if (cmine && e_in == 0) cnum[cf] = cnt;
+    }
+    __syncthreads();
+    // candidates of the chunk numbered face by face: start[f] face f's first
+    // (uniform)
+    int start[kGroupFaces + 1];
+    start[0] = 0;
+#pragma unroll
+    for (int f = 0; f < kGroupFaces; ++f) {
+      int c = f < F ? min(cnum[f] - skip, kc) : 0;
+      c = c > 0 ? c : 0;
+      start[f + 1] = start[f] + __builtin_amdgcn_readfirstlane(c);
+    }
+    const int total = start[kGroupFaces];
+    unsigned long long tlive[TPL];
+    bool inside[TPL], want[TPL];  // the tet lies inside a candidate; waits for its round
+#pragma unroll
+    for (int i = 0; i < TPL; ++i) {
+      tlive[i] = __ballot(todo[i]);
+      inside[i] = false;
+      want[i] = todo[i];
+    }
+    // batches of tets whose bits fit a word (one but for faces of more than
+    // kSmallFace points), and of these rounds of up to CAP pairs
+    int kb = 0;
+    for (;;) {
+      const int nb = tpf - kb < kBatch ? tpf - kb : kBatch;
+      // phase A, lanes over the candidates: tests into the tables wh (tets
+      // overlapped), wi (tets inside; bit 31: masks to be found pair by pair)
+      // and wc (tets cut by plane j).  The tables live in res, which phase B
+      // fills later.
+      uint32_t *wh = reinterpret_cast<uint32_t *>(res), *wi = wh + CAND, *wc = wi + CAND;
+      static_assert((2 + kRP) * CAND * 4 <= CAP * 8, "candidate tables in res");
+      for (int j0 = 0; j0 < total; j0 += kFastBlock / kPer) {
+        const int j = j0 + lane / kPer, part = kPer > 1 ? lane % kPer : 0;
+        const bool on = j < total && lane < (kFastBlock / kPer) * kPer;
+        uint32_t e = 0u, n[kRP];
+        int r = 0;
+        bool box = false, recut = false;
+#pragma unroll
+        for (int q = 0; q < kRP; ++q) n[q] = 0u;
+        if (on) {
+          int f = 0, at = 0;
+#pragma unroll
+          for (int i = 1; i < kGroupFaces; ++i) {
+            f += j >= start[i];
+            at = j >= start[i] ? start[i] : at;
+          }
+          r = f * kc + j - at;
+          // the face's tets of the batch that take part
+          const int b0 = f * tpf + kb;
+          unsigned long long tl = b0 < 64 ? tlive[0] >> b0 : 0ull;
+          if constexpr (TPL > 1)
+            tl |= b0 >= 64 ? tlive[TPL - 1] >> (b0 - 64) : (b0 > 0 ? tlive[TPL - 1] << (64 - b0) : 0ull);
+          const uint32_t all = (uint32_t)tl & (uint32_t)((1ull << nb) - 1ull);
+          const v3 c = mk3(fc[f][0], fc[f][1], fc[f][2]);
+          box = BOXES && (ccls[r] & 8);
+          if constexpr (BOXES) {
+            if (box) {
+              e = box_side_bits(part == 0 ? cbox[r][0] : (part == 1 ? cbox[r][1] : cbox[r][2]),
+                                part == 0 ? cbox[r][3] : (part == 1 ? cbox[r][4] : cbox[r][5]),
+                                part == 0 ? c.x : (part == 1 ? c.y : c.z), part, &vtx[f * nvf],
+                                &vtet[f * nvf], nvf, kb, all, n[0], n[1]);
+            } else if (part == 0) {
+              const int cell = ccell[r];
+              e = cand_tests<kRP>(m, mk3(cbox[r][0], cbox[r][1], cbox[r][2]),
+                                  mk3(cbox[r][3], cbox[r][4], cbox[r][5]), c, m.cf_off[cell],
+                                  m.npl[cell], &vtx[f * nvf], &vtet[f * nvf], nvf, kb, all, n,
+                                  recut);
+            }
+          } else {
+            const int cell = ccell[r];
+            e = cand_tests<kRP>(m, xyz(m.bblo[cell]), xyz(m.bbhi[cell]), c, ccq0[r], m.npl[cell],
+                                &vtx[f * nvf], &vtet[f * nvf], nvf, kb, all, n, recut);
+          }
+        }
+        uint32_t any = 0u;
+#pragma unroll
+        for (int q = 0; q < kRP; ++q) any |= n[q];
+        if constexpr (kPer > 1) {
+          const int l1 = lane - part + (part + 1) % kPer, l2 = lane - part + (part + 2) % kPer;
+          const uint32_t e1 = __shfl(e, l1), e2 = __shfl(e, l2);
+          const uint32_t a1 = __shfl(any, l1), a2 = __shfl(any, l2);
+          if (box) {
+            e &= e1 & e2;
+            any |= a1 | a2;
+            wc[2 * part * CAND + r] = n[0];
+            wc[(2 * part + 1) * CAND + r] = n[1];
+          }
+        }
+        if (on && part == 0) {
+          if (!box) {
+#pragma unroll
+            for (int q = 0; q < kRP; ++q) wc[q * CAND + r] = n[q];
+          }
+          wh[r] = e;
+          wi[r] = recut ? 1u << 31 : e & ~any;
+        }
       }
       __syncthreads();
-      // without chunks, a face with more candidates than its share goes to
-      // the general kernel
-      if constexpr (!CHUNKED) {
-        if (todo && cnum[fi] > kc) {
-          defer = true;
-          live = todo = false;
+      // lanes over the tets: the candidates of each of the lane's tets (bit ci
+      // of hits), up to the one it lies inside of
+      unsigned long long hits[TPL], ins[TPL];
+      int mcnt[TPL], mine = 0;  // pairs of each tet, and of the lane
+#pragma unroll
+      for (int i = 0; i < TPL; ++i) {
+        hits[i] = ins[i] = 0ull;
+        const int kt = k[i] - kb;  // the tet's bit
+        if (want[i] && kt < kBatch) {
+          const int nc = min(cnum[fi[i]] - skip, kc);
+          for (int ci = 0; ci < nc; ++ci) {
+            hits[i] |= (unsigned long long)((wh[fi[i] * kc + ci] >> kt) & 1u) << ci;
+            ins[i] |= (unsigned long long)((wi[fi[i] * kc + ci] >> kt) & 1u) << ci;
+          }
+          if (ins[i]) hits[i] &= ins[i] ^ (ins[i] - 1ull);
+        }
+        mcnt[i] = (int)__popcll(hits[i]);
+        mine += mcnt[i];
+      }
+      int mstart = mine;  // the lane's first pair
+      for (int o = 1; o < kFastBlock; o <<= 1) {
+        const int t = __shfl_up(mstart, o);
+        if (lane >= o) mstart += t;
+      }
+      const bool fits = mstart <= CAP;
+      const unsigned long long taken = __ballot(fits);
+      const int cnt = __shfl(mstart, 63 - __builtin_clzll(taken));
+      mstart -= mine;
+      int at = mstart;
+#pragma unroll
+      for (int i = 0; i < TPL; ++i) {
+        const int kt = k[i] - kb;
+        if (want[i] && kt < kBatch && fits) {
+          want[i] = false;
+          inside[i] = ins[i] != 0ull;
+          for (unsigned long long h = hits[i]; h; h &= h - 1ull) {
+            const int u = fi[i] * kc + __builtin_ctzll(h);
+            uint32_t mask = 0u;
+#pragma unroll
+            for (int q = 0; q < kRP; ++q) mask |= ((wc[q * CAND + u] >> kt) & 1u) << q;
+            qpair[at++] = mask | ((uint32_t)u << 16) |
+                          ((uint32_t)(lane + i * kFastBlock) << 24) | (wi[u] & (1u << 31));
+          }
+        } else {
+          mcnt[i] = 0;
         }
       }
-      // Phase A1, for cells that are not boxes: which candidates of its face
-      // may overlap each tet (bit ci of cmask), found with the lanes over the
-      // candidates (each loads its cell's bounds and planes once) and a loop
-      // over the face's tets (their vertices read from LDS).  The tests are
-      // those of pair_cuts_box in the same arithmetic, so phase A visits the
-      // pairs it would keep and skips the rest without loading anything; the
-      // first round of phase A also takes each pair's cutting-plane mask from
-      // A1 (a code byte per tet and candidate: 0x80 overlap, bits 0-3 the
-      // mask of the first four planes, 0x10 a cell of more planes, whose pair
-      // is tested again).  The tables live in res, which phase B fills only
-      // later.
-      unsigned long long cmask = ~0ull;
-      uint8_t *tcode = reinterpret_cast<uint8_t *>(res + kFastBlock);
-      static_assert(BOXES || 8 * kFastBlock + kFastBlock * 63 <= 8 * kCap, "A1 tables in res");
-      if constexpr (!BOXES) {
-        unsigned long long *tmask = reinterpret_cast<unsigned long long *>(res);
-        tmask[lane] = 0ull;
-        const int L = kFastBlock / F;  // lanes per face
-        const int cf = lane / L, cin = lane - cf * L;
-        const bool fok = cf < F && g * F + cf < count;
-        const int ncf = fok ? min(cnum[cf] - skip, kc) : 0;
-        int mostc = ncf;
-        for (int o = 32; o > 0; o >>= 1) mostc = max(mostc, __shfl_xor(mostc, o));
-        const unsigned long long seg = L >= 64 ? ~0ull : ((1ull << L) - 1ull);
-        const v3 cc = fok ? mk3(fc[cf][0], fc[cf][1], fc[cf][2]) : mk3(0, 0, 0);
-        __syncthreads();
-        for (int c0 = 0; c0 < mostc; c0 += L) {
-          const int ci = c0 + cin;
-          const bool has = ci < ncf;
-          int np = 0, q0 = 0;
-          double4 blo = make_double4(0, 0, 0, 0), bhi = blo;
-          Pl cp[4] = {Pl{0, 0, 0, 0}, Pl{0, 0, 0, 0}, Pl{0, 0, 0, 0}, Pl{0, 0, 0, 0}};
-          if (has) {
-            const int u = cf * kc + ci;
-            const int cell = ccell[u];
-            q0 = ccq0[u];
-            blo = m.bblo[cell];
-            bhi = m.bbhi[cell];
-            np = m.npl[cell];
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-              if (j < np) cp[j] = cell_plane_at(m, q0 + j, cc);
-          }
-          for (int k = 0; k < tpf; ++k) {
-            bool hit = false;
-            uint32_t cut = 0;
-            const int t = cf * tpf + k;
-            if (has) {
-              const v3 t1 = mk3(tv[0][t], tv[1][t], tv[2][t]);
-              const v3 t2 = mk3(tv[3][t], tv[4][t], tv[5][t]);
-              const v3 t3 = mk3(tv[6][t], tv[7][t], tv[8][t]);
+      __syncthreads();
+      {
+        // lanes over the pairs
+        int nbin[4] = {0, 0, 0, 0};
+        for (int p0 = 0; p0 < cnt; p0 += kFastBlock) {
+          const int item = p0 + lane;
+          int bin = -1;
+          if (item < cnt) {
+            uint32_t qp = qpair[item];
+            const int l = pair_tet(qp), u = pair_cand(qp), lf = tet_face(l, tpf);
+            const int cell = ccell[u], cl = ccls[u] & 7;
+            const bool box = BOXES && (ccls[u] & 8);
+            const v3 c = mk3(fc[lf][0], fc[lf][1], fc[lf][2]);
+            const Tet T = group_tet(tets, l);
+            uint32_t mask = qp & 0xffffu;
+            bool plic = cl == 1;
+            double val = 0.0;
+            bool out = false;
+            if (qp >> 31) {
               v3 lo, hi;
-              tet_bbox(cc, t1, t2, t3, lo, hi);
-              hit = !(hi.x <= blo.x || lo.x >= bhi.x || hi.y <= blo.y || lo.y >= bhi.y ||
-                      hi.z <= blo.z || lo.z >= bhi.z);
-              // plane j: false when the tet lies outside it, else its cut bit
-              auto test = [&](const Pl &pl, int j) {
-                const v3 nn = mk3(pl.x, pl.y, pl.z);
-                const double off = pl.w;
-                const double d1 = off - dot(nn, t1), d2 = off - dot(nn, t2),
-                             d3 = off - dot(nn, t3);
-                const double dmx = dmax(dmax(off, d1), dmax(d2, d3));
-                const double dmn = dmin(dmin(off, d1), dmin(d2, d3));
-                cut |= (dmn < 0.0 ? 1u : 0u) << (j & 3);
-                return dmx > 0.0;
-              };
-#pragma unroll
-              for (int j = 0; j < 4; ++j)
-                if (hit && j < np && !test(cp[j], j)) hit = false;
-              for (int j = 4; hit && j < np; ++j)
-                if (!test(cell_plane_at(m, q0 + j, cc), j)) hit = false;
-              tcode[t * kc + ci] = (uint8_t)(hit ? 0x80u | (cut & 15u) | (np > 4 ? 0x10u : 0u) : 0u);
+              tet_bbox(c, T.b, T.c, T.d, lo, hi);
+              out = pair_cuts(m, c, T, lo, hi, cell, mask) < 0;
+              qp = (qp & 0x7fff0000u) | mask;
+              qpair[item] = qp;
             }
-            const unsigned long long b = __ballot(hit);
-            if (fok && cin == 0) tmask[cf * tpf + k] |= ((b >> (cf * L)) & seg) << c0;
-          }
-        }
-        __syncthreads();
-        cmask = tmask[lane];
-      }
-      // Phases A to C in rounds: a tet whose queue is full stops at that pair
-      // and resumes there in the next round, once its queued pairs are added.
-      bool first = true;  // A1's code bytes are valid (res not yet written)
-      for (;;) {
-        int nq = 0;
-        if (todo) {
-          // the tet from its LDS row (kept there for phase B anyway)
-          const v3 c = mk3(fc[fi][0], fc[fi][1], fc[fi][2]);
-          const v3 t1 = mk3(tv[0][lane], tv[1][lane], tv[2][lane]);
-          const v3 t2 = mk3(tv[3][lane], tv[4][lane], tv[5][lane]);
-          const v3 t3 = mk3(tv[6][lane], tv[7][lane], tv[8][lane]);
-          const double det = tv[9][lane];
-          const Tet T{mk3(0, 0, 0), t1, t2, t3};
-          v3 lo, hi;
-          tet_bbox(c, t1, t2, t3, lo, hi);
-          const int nc = min(cnum[fi] - skip, kc);
-          bool paused = false, inside = false;
-          int ci = ci0;
-          for (; ci < nc; ++ci) {
-            if constexpr (!BOXES) {  // on to the next candidate phase A1 kept
-              const unsigned long long r = cmask >> ci;
-              if (!r) break;
-              ci += __builtin_ctzll(r);
-            }
-            const int u = fi * kc + ci;
-            const int cell = ccell[u];
-            const int cb = ccls[u];
-            const int cl = cb & 7;
-            const bool box = BOXES && (cb & 8);
-            const double *bb = cbox[BOXES ? u : 0];
-            uint32_t mask;
-            int ncut;
-            uint32_t code = 0;
-            if (!BOXES && first) code = tcode[lane * kc + ci];
-            if (!BOXES && (code & 0x90u) == 0x80u) {
-              mask = code & 15u;
-              ncut = __builtin_popcount(mask);
-            } else if (!BOXES) ncut = pair_cuts(m, c, T, lo, hi, cell, mask);
-            else if (box) ncut = box_cuts(bb, c, T, mask);
-            else
-              ncut = pair_cuts_box(m, c, T, lo, hi, mk3(bb[0], bb[1], bb[2]),
-                                   mk3(bb[3], bb[4], bb[5]), cell, mask);
-            if (ncut < 0) continue;
-            ++np;
+            const int ncut = __builtin_popcount(mask);
             // next to cell planes, the PLIC plane of an interface cell counts
             // only where it crosses the tet: with the tet wholly on its kept
             // side it drops out, wholly beyond it the pair holds no phase
-            bool plic = cl == 1;
-            if (plic && ncut > 0) {
-              const D4 dp = plane_dists(T, plic_plane_at(s, cell, c));
-              if (dmax(dmax(dp.a, dp.b), dmax(dp.c, dp.d)) <= 0.0) continue;
-              if (dmin(dmin(dp.a, dp.b), dmin(dp.c, dp.d)) >= 0.0) plic = false;
+            D4 d{0, 0, 0, 0};
+            if (plic) {
+              d = plane_dists(T, plic_plane_at(s, cell, c));
+              if (ncut > 0) {
+                out |= dmax(dmax(d.a, d.b), dmax(d.c, d.d)) <= 0.0;
+                if (dmin(dmin(d.a, d.b), dmin(d.c, d.d)) >= 0.0) plic = false;
+              }
             }
-            const int npl = ncut + (plic ? 1 : 0);
-            if (npl <= 1) {
+            const int npl = out ? 0 : ncut + (plic ? 1 : 0);
+            if (out) {
+              val = 0.0;
+            } else if (npl <= 1) {
               double fr = 1.0;
               if (npl == 1) {
-                const int q = __builtin_ctz(mask);
-                const Pl pl = !ncut ? plic_plane_at(s, cell, c)
-                                    : (box ? box_plane(bb, q, c)
-                                           : cell_plane_at(m, (BOXES ? m.cf_off[cell] : ccq0[u]) + q,
-                                                           c));
-                fr = tet_kept_fraction(plane_dists(T, pl));
+                if (ncut) {
+                  const int q = __builtin_ctz(mask);
+                  d = plane_dists(T, box ? box_plane(cbox[BOXES ? u : 0], q, c)
+                                         : cell_plane_at(m, (BOXES ? m.cf_off[cell] : ccq0[u]) + q,
+                                                         c));
+                }
+                fr = tet_kept_fraction(d);
               }
-              acc += class_weight(s, cell, cl) * det * fr;
+              val = class_weight(s, cell, cl) * tdet[l] * fr;
             } else if (npl > MAXPL) {
-              defer = true;
-              break;
-            } else if (nq == SLOTS) {
-              --np;  // counted again when the next round takes it
-              paused = true;
-              break;
+              tdef[l] = 1;
             } else {
-              qpair[nq * kFastBlock + lane] = mask | ((uint32_t)ci << 16) | (box ? 1u << 22 : 0u) |
-                                              ((uint32_t)(npl - 2) << 30);
-              ++nq;
+              bin = npl - 2;
             }
-            if (ncut == 0) {  // the tet lies inside this cell
-              inside = true;
-              break;
-            }
+            res[item] = val;
           }
-          if (defer) live = false;
-          todo = live && paused;
-          more = CHUNKED && live && !paused && !inside && cnum[fi] > skip + kc;
-          ci0 = todo ? ci : 0;
-          if (live) {
-            for (int j = 0; j < nq; ++j) {
-              int b = (int)(qpair[j * kFastBlock + lane] >> 30);
-              int pos = atomicAdd(&nbin[b], 1);
-              if (b >= 2) pos = kCap - 1 - pos;
-              bins[b == 0 || b == 3 ? 0 : 1][pos] = (uint16_t)(j * kFastBlock + lane);
+#pragma unroll
+          for (int b = 0; b < MAXPL - 1; ++b) {
+            const unsigned long long mb = __ballot(bin == b);
+            if (bin == b) {
+              int pos = nbin[b] + (int)__popcll(mb & lt);
+              if (b >= 2) pos = CAP - 1 - pos;
+              bins[b == 0 || b == 3 ? 0 : 1][pos] = (uint16_t)item;
             }
+            nbin[b] += (int)__popcll(mb);
           }
         }
         __syncthreads();
@@ -1566,84 +1769,109 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
         // faces share a group follows the order of the geometric-face list,
         // which is not fixed from run to run.
         const int32_t *q0s = BOXES ? nullptr : ccq0;
-        one_lane_bin<2>(m, s, qpair, tv, fc, ccell, ccls, q0s, cbox, tpf, kc, bins[0], nbin[0],
-                        false, kCap, res);
+        one_lane_bin<2>(m, s, qpair, tets, fc, ccell, ccls, q0s, cbox, tpf, bins[0], nbin[0],
+                        false, CAP, res);
         if constexpr (BOXES)
-          three_lane_bin<3>(m, s, qpair, tv, fc, ccell, ccls, q0s, cbox, tpf, kc, bins[1],
-                            nbin[1], false, kCap, res);
+          three_lane_bin<3>(m, s, qpair, tets, fc, ccell, ccls, q0s, cbox, tpf, bins[1], nbin[1],
+                            false, CAP, res);
         else
-          one_lane_bin<3>(m, s, qpair, tv, fc, ccell, ccls, q0s, cbox, tpf, kc, bins[1], nbin[1],
-                          false, kCap, res);
-        three_lane_bin<4>(m, s, qpair, tv, fc, ccell, ccls, q0s, cbox, tpf, kc, bins[1], nbin[2],
-                          true, kCap, res);
+          one_lane_bin<3>(m, s, qpair, tets, fc, ccell, ccls, q0s, cbox, tpf, bins[1], nbin[1],
+                          false, CAP, res);
+        three_lane_bin<4>(m, s, qpair, tets, fc, ccell, ccls, q0s, cbox, tpf, bins[1], nbin[2],
+                          true, CAP, res);
         if constexpr (MAXPL >= 5)
-          nine_lane_bin(m, s, qpair, tv, fc, ccell, ccls, q0s, tpf, kc, bins[0], nbin[3], kCap,
-                        res);
+          nine_lane_bin(m, s, qpair, tets, fc, ccell, ccls, q0s, tpf, bins[0], nbin[3], CAP, res);
         __syncthreads();
         // phase C
-        first = false;
-        if (live)
-          for (int j = 0; j < nq; ++j) acc += res[j * kFastBlock + lane];
-        if (!__ballot(todo)) break;
-        if (lane < 4) nbin[lane] = 0;
+        int from = mstart;
+#pragma unroll
+        for (int i = 0; i < TPL; ++i) {
+          for (int j = 0; j < mcnt[i]; ++j) acc[i] += res[from + j];
+          from += mcnt[i];
+          npt[i] += (unsigned)mcnt[i];
+        }
         __syncthreads();
       }
-      if (!__ballot(more)) break;
-      if (lane == 0) ++nresc;  // the group's stencils scanned again for the next chunk
-      todo = more;
-      more = false;
-      ci0 = 0;
-      if (lane < 4) nbin[lane] = 0;
-      __syncthreads();
+      // tets of the batch left for another round (their candidates are tested
+      // again: phase B has used the tables), else the next batch
+      bool left = false;
+#pragma unroll
+      for (int i = 0; i < TPL; ++i) left |= want[i] && k[i] - kb < kBatch;
+      if (!__ballot(left)) {
+        kb += kBatch;
+        if (kb >= tpf) break;
+      }
     }
-    if (live) {
-      npairs += np;
-      s.tetvol[idx] = sgn * acc / 6.0;
-    } else if (active && !defer) {
-      s.tetvol[idx] = 0.0;
+    bool again = false;
+#pragma unroll
+    for (int i = 0; i < TPL; ++i) {
+      if (tdef[lane + i * kFastBlock]) {
+        defer[i] = defer[i] || live[i];
+        live[i] = todo[i] = false;
+      }
+      todo[i] = todo[i] && !inside[i] && cnum[fi[i]] > skip + kc;
+      again |= todo[i];
     }
-    int q = wave_append(&s.work[kWDeferred], defer);
-    if (defer) s.defer[q] = (int32_t)idx;
+    if (!__ballot(again)) break;
+    if (lane == 0) ++nresc;  // the group's stencils scanned again for the next chunk
     __syncthreads();
   }
+#pragma unroll
+  for (int i = 0; i < TPL; ++i) {
+    const int64_t idx = ((int64_t)first + dir * (g * F + fi[i])) * m.tpf + k[i];
+    if (live[i]) {
+      npairs += (unsigned long long)npt[i];
+      s.tetvol[idx] = sgn[i] * acc[i] / 6.0;
+    } else if (active[i] && !defer[i]) {
+      s.tetvol[idx] = 0.0;
+    }
+    const int q = wave_append(&s.work[kWDeferred], defer[i]);
+    if (defer[i]) s.defer[q] = (int32_t)idx;
+  }
+  __syncthreads();
 }
 
-// Step 5 on the register path over one mesh: groups are taken kClaim at a
-// time, the first kClaim by block index, the rest claimed from a counter
-// (thousands of waves claiming one group each serialise on the counter's
-// atomic, above all at the start of the kernel).
-template <int SLOTS, int CAND, bool BOXES, int MAXPL, bool CHUNKED>
-__global__ __launch_bounds__(kFastBlock) __attribute__((amdgpu_waves_per_eu(BOXES ? 3 : 2)))
+// Face groups of a clip kernel: a block's first group by its index, every
+// further one claimed from the counter of its XCD (blockIdx.x mod 8), whose
+// claims run over every eighth group.  One counter for all waves is what
+// bounded the small groups: with thousands of waves each claim took its turn,
+// and claims of two groups at a time left the last of them with the chip
+// nearly empty (128^3 cubes: 150 us a step in claims of two).  The claim is
+// issued before the group's work, so that its answer is there at the end.
+struct GroupClaim {
+  int32_t *ctr;
+  int base, step;
+};
+__device__ __forceinline__ GroupClaim group_claim(int32_t *ctr, int stride) {
+  const int n = (int)gridDim.x < kXcds ? (int)gridDim.x : kXcds, x = (int)blockIdx.x % n;
+  return GroupClaim{ctr + x * stride, (int)gridDim.x + x, n};
+}
+__device__ __forceinline__ int claim_issue(const GroupClaim &c) {
+  return threadIdx.x == 0 ? atomicAdd(c.ctr, 1) : 0;
+}
+__device__ __forceinline__ int claim_group(const GroupClaim &c, int issued) {
+  return c.base + c.step * __builtin_amdgcn_readfirstlane(issued);
+}
+
+// Step 5 on the register path over one mesh.
+template <int TPL, int CAP, int CAND, bool BOXES, int MAXPL>
+__global__ __launch_bounds__(kFastBlock) __attribute__((amdgpu_waves_per_eu(2)))
 void k_clip_fast(DMesh m, DState s, DParams p) {
-  __shared__ int group;
-  const int lane = threadIdx.x;
   const int step = *s.stepno;
   const double sweep = -s.sc[step] * s.dt[step];
-  const ClipGroups cg = clip_groups(m, s);
+  const int gtets = group_tets<TPL>(geo_count(s), m.tpf);
+  const ClipGroups cg = clip_groups(m, s, gtets);
   const int ngroups = cg.total;
+  const GroupClaim claim = group_claim(claim_counter(s.cnt), kClaimStride);
   unsigned long long npairs = 0, nresc = 0;
-  int left = -1;
-  for (;;) {
-    if (lane == 0) {
-      if (left < 0) {
-        group = kClaim * (int)blockIdx.x;
-        left = kClaim;
-      } else if (left == 0) {
-        group = kClaim * ((int)gridDim.x + atomicAdd(&s.work[kWClipNext], 1));
-        left = kClaim;
-      } else {
-        group = group + 1;
-      }
-      --left;
-    }
-    __syncthreads();
-    const int g = group;
-    if (g >= ngroups) break;
+  for (int g = (int)blockIdx.x; g < ngroups;) {
+    const int next = claim_issue(claim);
     // one call site for both lists (the group body is inlined once)
     const bool sm = g < cg.nsmall;
-    clip_fast_group<SLOTS, CAND, BOXES, MAXPL, CHUNKED>(
+    clip_fast_group<TPL, CAP, CAND, BOXES, MAXPL>(
         m, s, p, sm ? g : g - cg.nsmall, sm ? cg.na : cg.nb, sm ? 0 : (int)m.nf - 1,
-        sm ? 1 : -1, sm ? cg.tsmall : m.tpf, sweep, npairs, nresc);
+        sm ? 1 : -1, sm ? cg.tsmall : m.tpf, gtets, sweep, npairs, nresc);
+    g = claim_group(claim, next);
   }
   wave_count(cnt_at(s.cnt, kCntPairs), npairs);
   wave_count(cnt_at(s.cnt, kCntRescans), nresc);
@@ -2089,6 +2317,7 @@ __device__ __forceinline__ void ledger_blk(const DMesh &m, const DState &s, cons
     s.stepno[0] += 1;  // the next step reads dt, scale at the next index
     for (int w = 0; w < kWNum; ++w) s.work[w] = 0;  // the next step's lists start empty
   }
+  if (threadIdx.x < kXcds) claim_counter(s.cnt)[threadIdx.x * kClaimStride] = 0;
 }
 __global__ __launch_bounds__(kLedgerBlock) void k_ledger(DMesh m, DState s, DParams p, int nparts) {
   ledger_blk(m, s, p, nparts);
@@ -2337,9 +2566,23 @@ __global__ __launch_bounds__(kBlock) void kb_group_prefix(BTab t) {
   for (int kind = 0; kind < kFaceKinds; ++kind) {
     const int kn = t.hdr[1 + kind];
     const int32_t *list = t.klist + kind * kMaxBatch;
+    // tets per group by the geometric faces of all the kind's meshes
+    __shared__ int faces, tpf;
+    if (threadIdx.x == 0) faces = tpf = 0;
+    __syncthreads();
+    for (int k = threadIdx.x; k < kn; k += blockDim.x) {
+      const BInst &I = t.inst[list[k]];
+      atomicAdd(&faces, geo_count(I.s));
+      atomicMax(&tpf, I.m.tpf);
+    }
+    __syncthreads();
+    const int gtets = kn == 0 ? kFastBlock
+                              : (kind == 0 ? group_tets<kTriTets>(faces, tpf)
+                                           : group_tets<kBoxTets>(faces, tpf));
+    if (threadIdx.x == 0) t.work[kBWTets + kind] = gtets;
     batch_prefix(kn, pre, [&](int k) {
       const BInst &I = t.inst[list[k]];
-      return clip_groups(I.m, I.s).total;
+      return clip_groups(I.m, I.s, gtets).total;
     });
     for (int k = threadIdx.x; k <= kn; k += blockDim.x)
       t.gpre[kind * (kMaxBatch + 1) + k] = pre[k];
@@ -2347,52 +2590,43 @@ __global__ __launch_bounds__(kBlock) void kb_group_prefix(BTab t) {
   }
 }
 
-template <int SLOTS, int CAND, bool BOXES, int MAXPL, bool CHUNKED>
-__global__ __launch_bounds__(kFastBlock) __attribute__((amdgpu_waves_per_eu(BOXES ? 3 : 2)))
-void kb_clip_fast(BTab t, int kind, int claim) {
-  __shared__ int group;
+template <int TPL, int CAP, int CAND, bool BOXES, int MAXPL>
+__global__ __launch_bounds__(kFastBlock) __attribute__((amdgpu_waves_per_eu(2)))
+void kb_clip_fast(BTab t, int kind, int most) {
   const int kn = t.hdr[1 + kind];
   const int32_t *list = t.klist + kind * kMaxBatch;
   const int32_t *pre = t.gpre + kind * (kMaxBatch + 1);
-  const int lane = threadIdx.x;
-  const int ngroups = pre[kn];
+  const int ngroups = pre[kn], gtets = t.work[kBWTets + kind];
+  const GroupClaim claim =
+      group_claim(t.work + kBWClip + kind * kXcds * kBWClipStride, kBWClipStride);
   unsigned long long npairs = 0, nresc = 0;
-  int cur = -1, left = -1;
-  for (;;) {
-    if (lane == 0) {
-      if (left < 0) {
-        group = claim * (int)blockIdx.x;
-        left = claim;
-      } else if (left == 0) {
-        group = claim * ((int)gridDim.x + atomicAdd(&t.work[kBWClip + kind], 1));
-        left = claim;
-      } else {
-        group = group + 1;
+  int cur = -1;
+  // `most` groups per claim where every block has several claims, else one
+  const int per = ngroups <= 4 * (int64_t)gridDim.x ? 1 : most;
+  for (int q = (int)blockIdx.x; (int64_t)q * per < ngroups;) {
+    const int next = claim_issue(claim);
+    for (int g = q * per; g < ngroups && g < (q + 1) * per; ++g) {
+      const int k = find_inst(pre, kn, g);
+      if (k != cur) {
+        if (cur >= 0) {
+          const DState &S = t.inst[list[cur]].s;
+          wave_count(cnt_at(S.cnt, kCntPairs), npairs);
+          wave_count(cnt_at(S.cnt, kCntRescans), nresc);
+        }
+        npairs = nresc = 0;
+        cur = k;
       }
-      --left;
+      const BInst &I = t.inst[list[k]];
+      const int step = *I.s.stepno;
+      const double sweep = -I.s.sc[step] * I.s.dt[step];
+      const ClipGroups cg = clip_groups(I.m, I.s, gtets);
+      const int gl = g - pre[k];
+      const bool sm = gl < cg.nsmall;
+      clip_fast_group<TPL, CAP, CAND, BOXES, MAXPL>(
+          I.m, I.s, I.p, sm ? gl : gl - cg.nsmall, sm ? cg.na : cg.nb, sm ? 0 : (int)I.m.nf - 1,
+          sm ? 1 : -1, sm ? cg.tsmall : I.m.tpf, gtets, sweep, npairs, nresc);
     }
-    __syncthreads();
-    const int g = group;
-    if (g >= ngroups) break;
-    const int k = find_inst(pre, kn, g);
-    if (k != cur) {
-      if (cur >= 0) {
-        const DState &S = t.inst[list[cur]].s;
-        wave_count(cnt_at(S.cnt, kCntPairs), npairs);
-        wave_count(cnt_at(S.cnt, kCntRescans), nresc);
-      }
-      npairs = nresc = 0;
-      cur = k;
-    }
-    const BInst &I = t.inst[list[k]];
-    const int step = *I.s.stepno;
-    const double sweep = -I.s.sc[step] * I.s.dt[step];
-    const ClipGroups cg = clip_groups(I.m, I.s);
-    const int gl = g - pre[k];
-    const bool sm = gl < cg.nsmall;
-    clip_fast_group<SLOTS, CAND, BOXES, MAXPL, CHUNKED>(
-        I.m, I.s, I.p, sm ? gl : gl - cg.nsmall, sm ? cg.na : cg.nb, sm ? 0 : (int)I.m.nf - 1,
-        sm ? 1 : -1, sm ? cg.tsmall : I.m.tpf, sweep, npairs, nresc);
+    q = claim_group(claim, next);
   }
   if (cur >= 0) {
     const DState &S = t.inst[list[cur]].s;
@@ -2458,7 +2692,8 @@ __global__ __launch_bounds__(kBlock) void kb_update(BTab t) {
 // one block per mesh; the first block also clears the batch's claim counters
 __global__ __launch_bounds__(kLedgerBlock) void kb_ledger(BTab t) {
   const int n = t.hdr[0];
-  if (blockIdx.x == 0 && threadIdx.x < kBWNum) t.work[threadIdx.x] = 0;
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < kBWNum; i += kLedgerBlock) t.work[i] = 0;
   if ((int)blockIdx.x >= n) return;
   const BInst &I = t.inst[blockIdx.x];
   ledger_blk(I.m, I.s, I.p, (int)grid_for_dev(I.m.nc, kBlock));
@@ -2570,11 +2805,11 @@ void launch_step(const DMesh &m, const DState &s, const DParams &p, hipStream_t 
   if (split) (void)hipStreamWaitEvent(st, fork->join, 0);
   if (m.maxn <= 3)
     TIMED(prof, kKClip,
-          (k_clip_fast<kTriSlots, kTriCand, false, kTriPlanes, true>
+          (k_clip_fast<kTriTets, kTriCap, kTriCand, false, kTriPlanes>
            <<<kFastGrid, kFastBlock, 0, st>>>(m, s, p)));
   else
     TIMED(prof, kKClip,
-          (k_clip_fast<kFastSlots, kCandPool, true, kFastPlanes, false>
+          (k_clip_fast<kBoxTets, kBoxCap, kBoxCand, true, kFastPlanes>
            <<<kFastGrid, kFastBlock, 0, st>>>(m, s, p)));
   TIMED(prof, kKClipGeneral, (k_clip_general<<<4096, kClipBlock, 0, st>>>(m, s, p)));
   TIMED(prof, kKFaceSum, (k_face_sum<<<1024, kBlock, 0, st>>>(m, s, p)));
@@ -2629,13 +2864,13 @@ void launch_batch_step(const BTab &t, const BConf &c, unsigned kinds, int ledger
   mark(3);
   kb_group_prefix<<<1, kBlock, 0, st>>>(t);
   if (kinds & 1u)
-    kb_clip_fast<kTriSlots, kTriCand, false, kTriPlanes, true>
+    kb_clip_fast<kTriTets, kTriCap, kTriCand, false, kTriPlanes>
         <<<c.grid_clip, kFastBlock, 0, st>>>(t, 0, c.clip_claim);
   if (kinds & 2u)
-    kb_clip_fast<kFastSlots, kCandPool, true, kFastPlanes, false>
+    kb_clip_fast<kBoxTets, kBoxCap, kBoxCand, true, kFastPlanes>
         <<<c.grid_clip, kFastBlock, 0, st>>>(t, 1, c.clip_claim);
   if (kinds & 4u)
-    kb_clip_fast<kFastSlots, kCandPool, true, kFastPlanes, false>
+    kb_clip_fast<kBoxTets, kBoxCap, kBoxCand, true, kFastPlanes>
         <<<c.grid_clip, kFastBlock, 0, st>>>(t, 2, c.clip_claim);
   mark(4);
   kb_clip_general<<<4096, kClipBlock, 0, st>>>(t);

@@ -61,8 +61,8 @@ constexpr int kCntStride = 16;
 constexpr int64_t kCntWords = (int64_t)kCntNum * kCntLanes * kCntStride;
 
 enum WorkCounter : int {
-  kWInterface = 0, kWGeometric = 1, kWDeferred = 2, kWClipNext = 3, kWWisps = 4, kWRecv = 5,
-  kWGeoLarge = 6, kWNum = 7
+  kWInterface = 0, kWGeometric = 1, kWDeferred = 2, kWWisps = 3, kWRecv = 4, kWGeoLarge = 5,
+  kWNum = 6
 };
 
 struct DMesh {
@@ -171,7 +171,12 @@ struct DState {
 constexpr int kMaxBatch = 256;
 constexpr int kFaceKinds = 3;  // 0: at most 3 points per face, 1: 4, 2: 5..8
 inline int face_kind(int maxn) { return maxn <= 3 ? 0 : (maxn == 4 ? 1 : 2); }
-enum BatchWork : int { kBWClip = 0, kBWNum = kBWClip + kFaceKinds };
+// Batch counters: the register clip's claims per face kind and XCD (a line
+// each), and its tets per group per face kind.
+constexpr int kBWClipStride = 32;
+enum BatchWork : int {
+  kBWClip = 0, kBWTets = kBWClip + kFaceKinds * 8 * kBWClipStride, kBWNum = kBWTets + kFaceKinds
+};
 struct BInst {
   DMesh m;
   DState s;   // the mesh's state, with dt / sc pointing at the batch's schedule
@@ -193,7 +198,7 @@ struct BTab {
 struct BConf {
   int grid_flux;     // persistent blocks of the flux kernel (multiple of 8)
   int grid_clip;     // waves of the register clip
-  int clip_claim;    // face groups taken per claim
+  int clip_claim;    // face groups taken per claim, at most
   int grid_plane;    // blocks of four waves for the plane kernel
   int grid_cells;    // blocks of the cell and point kernels
 };
