@@ -274,7 +274,8 @@ typedef struct {
   double alpha_min, alpha_max;
   int64_t wisps;              /* sum over steps of wisps found (wisps = 1)   */
   int64_t wisps_left;         /* of those, wisps with too little room around */
-  int64_t chunk_rescans;      /* face groups whose stencils were scanned again for a further chunk of
+  int64_t chunk_rescans;      /* face groups whose stencils were scanned again
+                                 for a further chunk of
                                  candidate cells (a face with more candidates
                                  than a group's share)                       */
 } vof_stats;

@@ -39,12 +39,16 @@ vof_status fail(vof_status code, const char *fmt, ...) {
 
 const char *last_error() { return g_err.c_str(); }
 
-vof_status flags_status(const uint32_t *d_flags) {
-  uint32_t fl = 0;
-  HIP_OR_FAIL(hipMemcpy(&fl, d_flags, sizeof fl, hipMemcpyDeviceToHost));
+vof_status flags_code(uint32_t fl) {
   if (fl & kFlagCapacity) return fail(VOF_ECAPACITY, "a clipped polytope exceeded its capacity");
   if (fl & kFlagLeak) return fail(VOF_ESTENCIL, "a flux polyhedron left its stencil");
   return VOF_OK;
+}
+
+vof_status flags_status(const uint32_t *d_flags) {
+  uint32_t fl = 0;
+  HIP_OR_FAIL(hipMemcpy(&fl, d_flags, sizeof fl, hipMemcpyDeviceToHost));
+  return flags_code(fl);
 }
 
 }  // namespace vof
@@ -502,7 +506,7 @@ vof_status vof_mesh_upload(vof_context *ctx, const vof_mesh_desc *d, vof_mesh **
   ALLOC(ds.defer, nf * (int64_t)dm.tpf);
   ALLOC(ds.stepno, 1); ALLOC(ds.work, kWNum); ALLOC(ds.cnt, kCntWords); ALLOC(ds.flags, 1); ALLOC(ds.ledger, 1);
   ALLOC(ds.part, (nc + 255) / 256 > 256 ? (nc + 255) / 256 : 256);
-  ALLOC(m->stats_buf, 4);
+  ALLOC(m->stats_buf, 1); ALLOC(m->stats_part, 4 * kStatsBlocks);
 #undef ALLOC
 #define UP(dst, src, n)                                                                    \
   do { if ((rc = to_device(dst, src, n, VOF_HOST, s))) { delete m; return rc; } } while (0)
@@ -914,16 +918,11 @@ vof_status vof_get_stats(vof_mesh *m, vof_stats *out) {
   vof_status rc = set_device(m->ctx);
   if (rc) return rc;
   hipStream_t s = m->ctx->stream;
-  launch_stats(m->dm, m->ds, m->stats_buf, s);
+  launch_stats(m->dm, m->ds, m->stats_part, m->stats_buf, s);
   HIP_OR_FAIL(hipGetLastError());
-  std::vector<unsigned long long> slots(kCntWords);
-  unsigned long long c[kCntNum] = {0};
-  double st4[4], led = 0.0;
-  if ((rc = from_device(slots.data(), m->ds.cnt, kCntWords, VOF_HOST, s))) return rc;
-  for (int id = 0; id < kCntNum; ++id)
-    for (int l = 0; l < kCntLanes; ++l) c[id] += slots[((int64_t)id * kCntLanes + l) * kCntStride];
-  if ((rc = from_device(st4, m->stats_buf, 4, VOF_HOST, s))) return rc;
-  if ((rc = from_device(&led, m->ds.ledger, 1, VOF_HOST, s))) return rc;
+  StatsOut st{};
+  if ((rc = from_device(&st, m->stats_buf, 1, VOF_HOST, s))) return rc;
+  const unsigned long long *c = st.cnt;
   out->steps = (int64_t)c[kCntSteps];
   out->face_fluxes = (int64_t)c[kCntFaceFluxes];
   out->geometric_faces = (int64_t)c[kCntGeometric];
@@ -935,14 +934,14 @@ vof_status vof_get_stats(vof_mesh *m, vof_stats *out) {
   out->correction_iters = (int64_t)c[kCntIters];
   out->clip_pairs = (int64_t)c[kCntPairs];
   out->general_tets = (int64_t)c[kCntDeferred];
-  out->ledger = led;
-  out->mass = st4[0];
-  out->alpha_min = st4[1];
-  out->alpha_max = st4[2];
+  out->ledger = st.ledger;
+  out->mass = st.mass;
+  out->alpha_min = st.alpha_min;
+  out->alpha_max = st.alpha_max;
   out->wisps = (int64_t)c[kCntWisps];
   out->wisps_left = (int64_t)c[kCntWispsLeft];
   out->chunk_rescans = (int64_t)c[kCntRescans];
-  return device_status(m);
+  return flags_code(st.flags);
 }
 
 vof_status vof_reset_stats(vof_mesh *m) {

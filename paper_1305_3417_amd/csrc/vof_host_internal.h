@@ -14,7 +14,9 @@ namespace vof {
 // Record a description of the failure for vof_last_error() and return code.
 vof_status fail(vof_status code, const char *fmt, ...);
 const char *last_error();
-// latched device flags (read after a synchronisation) -> status
+// latched device flags -> status
+vof_status flags_code(uint32_t fl);
+// the same from device memory (read after a synchronisation)
 vof_status flags_status(const uint32_t *d_flags);
 }  // namespace vof
 
@@ -41,7 +43,8 @@ struct vof_mesh {
   int64_t step_cap = 0;
   vof_context own_ctx{};
   bool have_alpha = false, have_velocity = false;
-  double *stats_buf = nullptr;  // 4 doubles
+  vof::StatsOut *stats_buf = nullptr;
+  double *stats_part = nullptr;  // 4 kStatsBlocks
   bool profiling = false;
   vof::Prof prof;
   // the launch sequence of one step captured once (valid while the kernel

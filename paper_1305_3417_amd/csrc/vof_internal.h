@@ -217,6 +217,13 @@ struct Prof {
   void end(int kid);
 };
 
+// What vof_get_stats reads from the device, in one copy.
+struct StatsOut {
+  double mass, alpha_min, alpha_max, ledger;
+  uint32_t flags;
+  unsigned long long cnt[kCntNum];
+};
+
 // launchers (vof_device.hip)
 void launch_mesh_geometry(const DMesh &m, double4 *X, const double *pts, double4 *S, double4 *C,
                           double *V, double4 *XC, double *wpc, double4 *cpl, uint8_t *npl,
@@ -234,7 +241,8 @@ struct Fork {
 void launch_step(const DMesh &m, const DState &s, const DParams &p, hipStream_t st, Prof *prof,
                  const Fork *fork);
 void launch_reconstruct(const DMesh &m, const DState &s, const DParams &p, hipStream_t st);
-void launch_stats(const DMesh &m, const DState &s, double *out4, hipStream_t st);
+constexpr int kStatsBlocks = 1024;
+void launch_stats(const DMesh &m, const DState &s, double *part, StatsOut *out, hipStream_t st);
 void launch_map_alpha(const DMesh &d, double *alpha, const int32_t *off, const int32_t *cells,
                       const DMesh &o, const DState &os, uint32_t *flags, hipStream_t st);
 // One batch step on `st` (plane kernel on fork->side when given).  `kinds`
