@@ -892,7 +892,7 @@ __global__ void k_face_coeffs(DMesh m, const double *XU, double *coef) {
 // The faces base .. base + blockDim.x - 1 of one mesh, one per thread.
 template <int NMAX>
 __device__ __forceinline__ void flux_chunk(const DMesh &m, const DState &s, const DParams &p,
-                                           int64_t base, double dt, double sc,
+                                           int64_t base, double dt, double sc, bool last,
                                            unsigned long long &nflux, unsigned long long &nit,
                                            unsigned long long &nbad) {
     const int64_t f = base + threadIdx.x;
@@ -906,6 +906,8 @@ __device__ __forceinline__ void flux_chunk(const DMesh &m, const DState &s, cons
 #pragma unroll
         for (int i = 0; i < NMAX; ++i) nq += q[i] >= 0;
       }
+      // the face's kind of the step before: kinds 0 and 1 hold a phase volume of 0
+      const uint8_t was = __builtin_nontemporal_load(&s.kind[f]);
       double F = sc * __builtin_nontemporal_load(&s.F0[f]);
       double T = F * dt;
       double lam = 0.0, vph = 0.0;
@@ -956,11 +958,18 @@ __device__ __forceinline__ void flux_chunk(const DMesh &m, const DState &s, cons
         }
         s.fbulk[f] = mask == 1 ? 1 : (mask == 2 ? 2 : 0);
       }
-      __builtin_nontemporal_store(lam, &s.lam[f]);
-      if (!geo) __builtin_nontemporal_store(vph, &s.vphase[f]);
-      __builtin_nontemporal_store((uint8_t)(it > 255 ? 255 : it), &s.iters[f]);
-      __builtin_nontemporal_store(kind, &s.kind[f]);
-      __builtin_nontemporal_store((uint8_t)stat, &s.fstatus[f]);
+      // The step itself needs lambda and the status of the geometric faces
+      // only, and the kinds and phase volumes that change; the rest is what
+      // vof_read_face shows, written by the last step of a call.  (67 bytes a
+      // face with every output written, 49 without; 128^3 cubes 112 us, now 103:
+      // the correction's arithmetic bounds the rest.)
+      if (geo || last) {
+        __builtin_nontemporal_store(lam, &s.lam[f]);
+        __builtin_nontemporal_store((uint8_t)stat, &s.fstatus[f]);
+      }
+      if (last) __builtin_nontemporal_store((uint8_t)(it > 255 ? 255 : it), &s.iters[f]);
+      if (!geo && (kind > 1 || was > 1)) __builtin_nontemporal_store(vph, &s.vphase[f]);
+      if (kind != was) s.kind[f] = kind;
     }
     bool large = false;
     if constexpr (NMAX > kSmallFace) {
@@ -976,6 +985,7 @@ template <int NMAX>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(NMAX <= 4 ? 4 : 1)))
 void k_flux(DMesh m, DState s, DParams p) {
   const int step = *s.stepno;
+  const bool last = step + 1 == s.stepno[1];
   const double dt = s.dt[step], sc = s.sc[step];
   // every XCD walks one contiguous range of the face blocks with its blocks
   // side by side (a grid of about the resident blocks moves as one front),
@@ -987,7 +997,7 @@ void k_flux(DMesh m, DState s, DParams p) {
   const int64_t b1 = nb * (x + 1) / kXcds;
   unsigned long long nflux = 0, nit = 0, nbad = 0;
   for (int64_t b = nb * x / kXcds + j; b < b1; b += per)
-    flux_chunk<NMAX>(m, s, p, b * blockDim.x, dt, sc, nflux, nit, nbad);
+    flux_chunk<NMAX>(m, s, p, b * blockDim.x, dt, sc, last, nflux, nit, nbad);
   block_count3(cnt_at(s.cnt, kCntFaceFluxes), nflux, cnt_at(s.cnt, kCntIters), nit, cnt_at(s.cnt, kCntUnreached), nbad);
 }
 
@@ -2128,6 +2138,19 @@ __device__ __forceinline__ void update_blk(const DMesh &m, const DState &s, cons
         }
       }
     }
+    if (!skip && !p.wisps) {
+      // a cell whose faces all carry nothing (kinds 0 and 1) keeps its alpha:
+      // one byte a face, shared by two cells, instead of its phase volume, the
+      // cell's volume and alpha (31 bytes a cell against 79; 128^3 cubes 28.7
+      // us, now 19.0; 80^3 x 6 tetrahedra 52, now 35)
+      bool flow = false;
+#pragma unroll 6
+      for (int k = k0; k < k1; ++k) {
+        const int sf = m.cf[k];
+        flow |= s.kind[sf >= 0 ? sf : ~sf] > 1;
+      }
+      skip = !flow;
+    }
     if (!skip) {
       double acc = 0.0;
       // unrolled so that the face ids, then the phase volumes, load together
@@ -2501,10 +2524,12 @@ __device__ void batch_prefix(int n, int32_t *pre, Units units) {
   __syncthreads();
 }
 
-__global__ __launch_bounds__(kBlock) void kb_begin(BTab t) {
+__global__ __launch_bounds__(kBlock) void kb_begin(BTab t, int n_steps) {
   const int n = t.hdr[0];
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
     t.inst[i].s.stepno[0] = 0;
+    t.inst[i].s.stepno[1] = n_steps;
+  }
 }
 
 __global__ __launch_bounds__(kBlock) void kb_cell_class(BTab t) {
@@ -2578,7 +2603,7 @@ void kb_flux(BTab t, int kind) {
     const BInst &I = t.inst[list[k]];
     const int step = *I.s.stepno;
     flux_chunk<NMAX>(I.m, I.s, I.p, (int64_t)(g - off[k]) * blockDim.x, I.s.dt[step],
-                     I.s.sc[step], nflux, nit, nbad);
+                     I.s.sc[step], step + 1 == I.s.stepno[1], nflux, nit, nbad);
   }
   if (cur >= 0) {
     const DState &S = t.inst[list[cur]].s;
@@ -2854,8 +2879,8 @@ void launch_step(const DMesh &m, const DState &s, const DParams &p, hipStream_t 
         (k_ledger<<<1, kLedgerBlock, 0, st>>>(m, s, p, (int)grid_for(m.nc, kBlock))));
 }
 
-void launch_batch_begin(const BTab &t, int n, hipStream_t st) {
-  if (n > 0) kb_begin<<<grid_for(n, kBlock), kBlock, 0, st>>>(t);
+void launch_batch_begin(const BTab &t, int n, int n_steps, hipStream_t st) {
+  if (n > 0) kb_begin<<<grid_for(n, kBlock), kBlock, 0, st>>>(t, n_steps);
 }
 
 // One step of a batch: the single-mesh step's kernels, each over all meshes

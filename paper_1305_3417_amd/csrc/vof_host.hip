@@ -504,7 +504,7 @@ vof_status vof_mesh_upload(vof_context *ctx, const vof_mesh_desc *d, vof_mesh **
   ALLOC(ds.vphase, nf); ALLOC(ds.vscale, nf); ALLOC(ds.coef, 3 * nf); ALLOC(ds.iters, nf); ALLOC(ds.kind, nf); ALLOC(ds.fstatus, nf);
   ALLOC(ds.icells, nc); ALLOC(ds.gfaces, nf); ALLOC(ds.tetvol, nf * (int64_t)dm.tpf);
   ALLOC(ds.defer, nf * (int64_t)dm.tpf);
-  ALLOC(ds.stepno, 1); ALLOC(ds.work, kWNum); ALLOC(ds.cnt, kCntWords); ALLOC(ds.flags, 1); ALLOC(ds.ledger, 1);
+  ALLOC(ds.stepno, 2); ALLOC(ds.work, kWNum); ALLOC(ds.cnt, kCntWords); ALLOC(ds.flags, 1); ALLOC(ds.ledger, 1);
   ALLOC(ds.part, (nc + 255) / 256 > 256 ? (nc + 255) / 256 : 256);
   ALLOC(m->stats_buf, 1); ALLOC(m->stats_part, 4 * kStatsBlocks);
 #undef ALLOC
@@ -775,8 +775,8 @@ vof_status vof_advect(vof_mesh *m, int32_t n_steps, const double *dt, const doub
   }
   HIP_OR_FAIL(hipMemcpy(m->ds.dt, dt, sizeof(double) * n_steps, hipMemcpyHostToDevice));
   HIP_OR_FAIL(hipMemcpy(m->ds.sc, scale, sizeof(double) * n_steps, hipMemcpyHostToDevice));
-  const int32_t first = 0;
-  HIP_OR_FAIL(hipMemcpy(m->ds.stepno, &first, sizeof first, hipMemcpyHostToDevice));
+  const int32_t first[2] = {0, n_steps};
+  HIP_OR_FAIL(hipMemcpy(m->ds.stepno, first, sizeof first, hipMemcpyHostToDevice));
   if (m->profiling) {
     // room for every kernel of every step; pairs are folded into totals by
     // vof_read_profile
@@ -829,11 +829,11 @@ vof_status vof_advect_noalloc(vof_mesh *m, int32_t n_steps, const double *dt,
   hipStream_t s = m->ctx->stream;
   // schedule and step counter staged in stream order behind earlier work of
   // this mesh; the host arrays may be reused once the call returns
-  const int32_t first = 0;
+  const int32_t first[2] = {0, n_steps};
   HIP_OR_FAIL(hipMemcpyAsync(ptr, dt, sizeof(double) * n_steps, hipMemcpyHostToDevice, s));
   HIP_OR_FAIL(hipMemcpyAsync(ptr + VOF_NOALLOC_MAX_STEPS, scale, sizeof(double) * n_steps,
                              hipMemcpyHostToDevice, s));
-  HIP_OR_FAIL(hipMemcpyAsync(m->ds.stepno, &first, sizeof first, hipMemcpyHostToDevice, s));
+  HIP_OR_FAIL(hipMemcpyAsync(m->ds.stepno, first, sizeof first, hipMemcpyHostToDevice, s));
   HIP_OR_FAIL(hipStreamSynchronize(s));
   DState ds = m->ds;
   ds.dt = ptr;

@@ -144,7 +144,8 @@ struct DState {
   uint32_t *flags;      // latched status bits
   double *ledger;       // accumulated boundary phase volume
   double *part;         // per update block: its cells' boundary phase volume
-  int32_t *stepno;      // index into dt / sc of the step being run
+  int32_t *stepno;      // [0] index into dt / sc of the step being run, [1] the call's steps
+                        // (the last one writes every face's outputs; 0: none does)
   double *dt;           // per-step dt (device copy)
   double *sc;           // per-step scale
   // narrow band
@@ -253,7 +254,7 @@ void launch_map_alpha(const DMesh &d, double *alpha, const int32_t *off, const i
 void launch_batch_step(const BTab &t, const BConf &c, unsigned kinds, int ledger_grid,
                        hipStream_t st, const Fork *fork, hipEvent_t *ev = nullptr);
 // Set every mesh's step counter to 0 (before a batch's first step).
-void launch_batch_begin(const BTab &t, int n, hipStream_t st);
+void launch_batch_begin(const BTab &t, int n, int n_steps, hipStream_t st);
 double host_tet_clip(const double *tet, int n_planes, const double *planes);
 double host_tet_clip_closed(const double *tet, int n_planes, const double *planes);
 

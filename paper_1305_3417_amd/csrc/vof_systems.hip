@@ -206,8 +206,8 @@ struct BatchCore {
   }
 
   // every mesh's step counter to 0 (before the first of a run of steps)
-  vof_status begin() {
-    launch_batch_begin(tab, n, stream);
+  vof_status begin(int32_t n_steps) {
+    launch_batch_begin(tab, n, n_steps, stream);
     HIP_OR_FAIL(hipGetLastError());
     return VOF_OK;
   }
@@ -360,7 +360,7 @@ vof_status batch_prepare(vof_batch *b, int32_t n_steps, const double *dt, const 
   }
   vof_status rc = b->core.set(e.data(), n);
   if (rc) return rc;
-  return b->core.begin();
+  return b->core.begin(n_steps);
 }
 
 }  // namespace
@@ -612,7 +612,7 @@ StateLayout state_layout(const DMesh &m, int64_t steps) {
   L.ledger = take(8);
   const size_t nparts = std::max<size_t>((nc + 255) / 256, 256);
   L.part = take(8 * nparts);
-  L.stepno = take(4);
+  L.stepno = take(8);
   L.dt = take(8 * (size_t)steps);
   L.sc = take(8 * (size_t)steps);
   L.bytes = o;
@@ -750,7 +750,8 @@ vof_status job_admit(vof_server *S, vof_job *j) {
   HIP_OR_FAIL(hipMemsetAsync(d.cnt, 0, 8 * (size_t)kCntWords, s));
   HIP_OR_FAIL(hipMemsetAsync(d.flags, 0, 4, s));
   HIP_OR_FAIL(hipMemsetAsync(d.ledger, 0, 8, s));
-  HIP_OR_FAIL(hipMemsetAsync(d.stepno, 0, 4, s));
+  HIP_OR_FAIL(hipMemsetAsync(d.stepno, 0, 8, s));  // a job's faces are never read
+  HIP_OR_FAIL(hipMemsetAsync(d.kind, 0, (size_t)m.nf, s));
   HIP_OR_FAIL(hipMemsetAsync(d.cls, 0, (size_t)m.nc, s));
   HIP_OR_FAIL(hipMemsetAsync(d.plane, 0, 32 * (size_t)m.nc, s));
   HIP_OR_FAIL(hipMemsetAsync(d.lam, 0, 8 * (size_t)m.nf, s));
