@@ -1446,6 +1446,9 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
   __shared__ double cbox[BOXES ? CAND : 1][6];
   __shared__ double fbox[kGroupFaces][6];
   __shared__ int cnum[kGroupFaces];
+  // phase A's tables, kept over the rounds
+  __shared__ uint2 whi[CAND];
+  __shared__ uint32_t wc[kRP * CAND];
   __shared__ uint8_t tdef[TPL * kFastBlock];  // tets left to the general clip
   const int lane = threadIdx.x;
   const int F = gtets / tpf;       // faces per group, 1..kGroupFaces
@@ -1644,16 +1647,13 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
     }
     // batches of tets whose bits fit a word (one but for faces of more than
     // kSmallFace points), and of these rounds of up to CAP pairs
-    int kb = 0;
+    int kb = 0, tested = -1;
     for (;;) {
       const int nb = tpf - kb < kBatch ? tpf - kb : kBatch;
-      // phase A, lanes over the candidates: tests into the tables wh (tets
-      // overlapped), wi (tets inside; bit 31: masks to be found pair by pair)
-      // and wc (tets cut by plane j).  The tables live in res, which phase B
-      // fills later.
-      uint32_t *wh = reinterpret_cast<uint32_t *>(res), *wi = wh + CAND, *wc = wi + CAND;
-      static_assert((2 + kRP) * CAND * 4 <= CAP * 8, "candidate tables in res");
-      for (int j0 = 0; j0 < total; j0 += kFastBlock / kPer) {
+      // phase A, lanes over the candidates: tests into the tables whi (tets
+      // overlapped, and tets inside; bit 31 of these: masks to be found pair by
+      // pair) and wc (tets cut by plane j), once per batch
+      for (int j0 = 0; j0 < (tested == kb ? 0 : total); j0 += kFastBlock / kPer) {
         const int j = j0 + lane / kPer, part = kPer > 1 ? lane % kPer : 0;
         const bool on = j < total && lane < (kFastBlock / kPer) * kPer;
         uint32_t e = 0u, n[kRP];
@@ -1715,10 +1715,10 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
 #pragma unroll
             for (int q = 0; q < kRP; ++q) wc[q * CAND + r] = n[q];
           }
-          wh[r] = e;
-          wi[r] = recut ? 1u << 31 : e & ~any;
+          whi[r] = make_uint2(e, recut ? 1u << 31 : e & ~any);
         }
       }
+      tested = kb;
       __syncthreads();
       // lanes over the tets: the candidates of each of the lane's tets (bit ci
       // of hits), up to the one it lies inside of
@@ -1730,9 +1730,11 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
         const int kt = k[i] - kb;  // the tet's bit
         if (want[i] && kt < kBatch) {
           const int nc = min(cnum[fi[i]] - skip, kc);
+#pragma unroll 4
           for (int ci = 0; ci < nc; ++ci) {
-            hits[i] |= (unsigned long long)((wh[fi[i] * kc + ci] >> kt) & 1u) << ci;
-            ins[i] |= (unsigned long long)((wi[fi[i] * kc + ci] >> kt) & 1u) << ci;
+            const uint2 b = whi[fi[i] * kc + ci];
+            hits[i] |= (unsigned long long)((b.x >> kt) & 1u) << ci;
+            ins[i] |= (unsigned long long)((b.y >> kt) & 1u) << ci;
           }
           if (ins[i]) hits[i] &= ins[i] ^ (ins[i] - 1ull);
         }
@@ -1761,7 +1763,7 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
 #pragma unroll
             for (int q = 0; q < kRP; ++q) mask |= ((wc[q * CAND + u] >> kt) & 1u) << q;
             qpair[at++] = mask | ((uint32_t)u << 16) |
-                          ((uint32_t)(lane + i * kFastBlock) << 24) | (wi[u] & (1u << 31));
+                          ((uint32_t)(lane + i * kFastBlock) << 24) | (whi[u].y & (1u << 31));
           }
         } else {
           mcnt[i] = 0;
@@ -1868,8 +1870,7 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
         }
         __syncthreads();
       }
-      // tets of the batch left for another round (their candidates are tested
-      // again: phase B has used the tables), else the next batch
+      // tets of the batch left for another round, else the next batch
       bool left = false;
 #pragma unroll
       for (int i = 0; i < TPL; ++i) left |= want[i] && k[i] - kb < kBatch;
