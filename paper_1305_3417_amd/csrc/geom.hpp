@@ -278,6 +278,32 @@ VHD double kept_fraction(TD<K> T) {
   return acc;
 }
 
+// A plane that keeps exactly one vertex of T (its distances in d) leaves one
+// tetrahedron, so it is applied first where a pair has such a plane: D, the
+// distances to the other K planes, becomes that of the kept corner, and the
+// result is the corner's volume ratio.  (The parameters are clamped: the one
+// kept vertex may have been found with other rounding.)
+template <int K>
+VHD double corner_cut(D4 d, TD<K> &D) {
+  const bool kb = d.b >= 0.0, kc = d.c >= 0.0 && !kb, ke = d.d >= 0.0 && !kb && !kc;
+  const double a = kb ? d.b : (kc ? d.c : (ke ? d.d : d.a));
+  const VD<K> A = sel(kb, D.b, sel(kc, D.c, sel(ke, D.e, D.a)));
+  auto cut = [&](bool moved, const VD<K> &own, double down, double &r) {
+    const VD<K> v = sel(moved, D.a, own);
+    const double dv = moved ? d.a : down;
+    const double t = dmin(dmax(quot(a, dmax(a - dv, 1e-290)), 0.0), 1.0);
+    VD<K> o;
+#pragma unroll
+    for (int k = 0; k < K; ++k) o.d[k] = A.d[k] + t * (v.d[k] - A.d[k]);
+    r *= t;
+    return o;
+  };
+  double r = 1.0;
+  const VD<K> b = cut(kb, D.b, d.b, r), c = cut(kc, D.c, d.c, r), e = cut(ke, D.e, d.d, r);
+  D = TD<K>{A, b, c, e};
+  return r;
+}
+
 // A plane n.x = s as four plain doubles (plain aggregates stay in registers
 // through selects, unlike the union-based vector types).
 struct Pl {

@@ -19,6 +19,7 @@
 
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "geom.hpp"
 #include "vof_internal.h"
@@ -41,7 +42,7 @@ constexpr int kFastBlock = 64;   // one wave per block in the register clip
 // tetrahedral meshes (58 stencil cells, about 7 overlapping cells per flux
 // tet) the second, at two to three waves per SIMD.
 constexpr int kBoxTets = 2, kBoxCap = 304, kBoxCand = 72;
-constexpr int kTriTets = 1, kTriCap = 640, kTriCand = 192;
+constexpr int kTriTets = 1, kTriCap = 608, kTriCand = 192;
 constexpr int kFastPlanes = 4;   // planes per pair in the register clip (more: general)
 constexpr int kTriPlanes = 5;    // the same for triangle faces
 constexpr int kFastGrid = 4096;   // blocks claim face groups from counters
@@ -1120,9 +1121,20 @@ __device__ __forceinline__ unsigned long long tets_of(int n, int i, int which) {
   return 30ull << a;                                    // 5i+1 .. 5i+4
 }
 
-// A pair of the register clip in LDS: cutting-plane mask (bits 0-15),
-// candidate row (16-23), tet (24-30), and bit 31 where the mask is still to
-// be found (a cell of more planes than the candidate tests keep).
+// A pair of the register clip in LDS: candidate row (bits 16-23), tet (24-30),
+// and in bits 0-7 the mask of the cell planes that cut the tet, in bits 8-15
+// those of them that keep one of its vertices only.  With bit 31 (a cell of
+// more planes than the candidate tests keep) bits 0-15 are the mask, found
+// pair by pair.
+// A bin's entry: the pair (bits 0-9) and its leading plane (10-13): 0 none,
+// 1 + j cell plane j, kLeadPlic the PLIC plane.
+constexpr int kLeadPlic = 15;
+__device__ __forceinline__ uint32_t pair_mask(uint32_t qp) {
+  return qp & (qp >> 31 ? 0xffffu : 0xffu);
+}
+__device__ __forceinline__ uint32_t pair_corners(uint32_t qp) {
+  return qp >> 31 ? 0u : (qp >> 8) & 0xffu;
+}
 __device__ __forceinline__ int pair_tet(uint32_t qp) { return (int)(qp >> 24) & 127; }
 __device__ __forceinline__ int pair_cand(uint32_t qp) { return (int)(qp >> 16) & 255; }
 __device__ __forceinline__ int tet_face(int l, int tpf) {
@@ -1148,121 +1160,121 @@ __device__ __forceinline__ Tet group_tet(const GroupTets &t, int l) {
   return Tet{mk3(0, 0, 0), vtx_at(t.vtx, r), vtx_at(t.vtx, r >> 8), vtx_at(t.vtx, r >> 16)};
 }
 
-// The pair's tet, its six-fold volume, the cell, its
-// class and its planes in mask order (then the PLIC plane of an interface
-// cell).  The candidate's class comes from LDS, and so does its first plane
-// index when the kernel stages it (ccq0, cells that are not boxes), so the
-// plane loads do not wait on other loads.
-__device__ __forceinline__ void queued_pair(const DMesh &m, const DState &s, const uint32_t *qpair,
-                                            const GroupTets &tets,
-                                            const double (*fc)[3], const int32_t *ccell,
-                                            const int8_t *ccls, const int32_t *ccq0,
-                                            const double (*cbox)[6], int tpf, int item,
-                                            Tet &T, double &det, int &cell, int &cl, Pl &p0,
-                                            Pl &p1, Pl &p2, Pl &p3) {
-  const uint32_t qp = qpair[item];
-  const int l = pair_tet(qp), u = pair_cand(qp), lf = tet_face(l, tpf);
-  cell = ccell[u];
-  const v3 c = mk3(fc[lf][0], fc[lf][1], fc[lf][2]);
-  T = group_tet(tets, l);
-  det = tets.det[l];
-  cl = ccls[u] & 7;
-  if (ccls[u] & 8)
-    pair_regs_box(cbox[u], s, c, cell, cl, qp & 0xffffu, p0, p1, p2, p3);
-  else
-    pair_regs_q(m, s, c, cell, cl, ccq0 ? ccq0[u] : m.cf_off[cell], qp & 0xffffu, p0, p1, p2,
-                p3);
+// What phase B reads of a group's LDS: the tets, face centres, candidates
+// (cell, class, first plane index of cells that are not boxes, bounds of the
+// others), the pairs and their results.
+struct GroupData {
+  GroupTets tets;
+  const double (*fc)[3];
+  const int32_t *ccell;
+  const int8_t *ccls;
+  const int32_t *ccq0;       // null: from cf_off (kernels of box cells)
+  const double (*cbox)[6];
+  const uint32_t *qpair;
+  double *res;
+  int tpf;
+};
+
+// A binned pair's tet, six-fold volume times class weight, and the distances
+// of the tet's vertices to the pair's R planes: its cutting planes in mask
+// order, then the PLIC plane of an interface cell.  With a leading plane
+// (one that keeps a single vertex) there are R + 1 planes; the tet is then
+// the corner that plane keeps, and `ratio` the corner's share of the tet.
+template <int R>
+__device__ __forceinline__ TD<R> pair_table(const DMesh &m, const DState &s, const GroupData &G,
+                                            uint16_t entry, int &item, double &vol, double &ratio) {
+  item = entry & 1023;
+  const int lead = entry >> 10;
+  const uint32_t qp = G.qpair[item];
+  const int l = pair_tet(qp), u = pair_cand(qp), lf = tet_face(l, G.tpf);
+  const int cell = G.ccell[u], cb = G.ccls[u], cl = cb & 7;
+  const bool box = cb & 8;
+  const v3 c = mk3(G.fc[lf][0], G.fc[lf][1], G.fc[lf][2]);
+  const Tet T = group_tet(G.tets, l);
+  vol = class_weight(s, cell, cl) * G.tets.det[l];
+  const Pl pl = cl == 1 ? plic_plane_at(s, cell, c) : Pl{0, 0, 0, 0};
+  const int q0 = box ? 0 : (G.ccq0 ? G.ccq0[u] : m.cf_off[cell]);
+  auto plane = [&](int j) { return box ? box_plane(G.cbox[u], j, c) : cell_plane_at(m, q0 + j, c); };
+  uint32_t mm = pair_mask(qp);
+  Pl first = pl;
+  if (lead != 0 && lead != kLeadPlic) {
+    first = plane(lead - 1);
+    mm &= ~(1u << (lead - 1));
+  }
+  Pl p[4] = {pl, pl, pl, pl};
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    if (mm) p[k] = plane(__builtin_ctz(mm));
+    mm &= mm - 1;
+  }
+  TD<R> D = dist_table<R>(T, p[0], p[1], p[2], p[3]);
+  ratio = 1.0;
+  if (lead) ratio = corner_cut<R>(plane_dists(T, first), D);
+  return D;
 }
 
-// A phase-B bin of pairs of K planes, three lanes per pair (one per term of
-// the first plane's split; 21 pairs per pass).  The bin's items are bin[t],
-// or bin[cap - 1 - t] for a bin filled from the end.
-template <int K>
+// A phase-B bin of pairs of R planes (beside their leading plane), one lane
+// per pair: the whole recursion of the closed form in the pair's lane.  The
+// bin's entries are bin[t], or bin[cap - 1 - t] for a bin filled from the end.
+template <int R>
+__device__ __forceinline__ void one_lane_bin(const DMesh &m, const DState &s, const GroupData &G,
+                                             const uint16_t *bin, int cnt) {
+  for (int t = (int)threadIdx.x; t < cnt; t += kFastBlock) {
+    int item;
+    double vol, ratio;
+    const TD<R> D = pair_table<R>(m, s, G, bin[t], item, vol, ratio);
+    G.res[item] = vol * (ratio * kept_fraction<R>(D));
+  }
+}
+
+// The same with three lanes per pair (one per term of the first plane's split;
+// 21 pairs per pass).
+template <int R>
 __device__ __forceinline__ void three_lane_bin(const DMesh &m, const DState &s,
-                                               const uint32_t *qpair,
-                                               const GroupTets &tets,
-                                               const double (*fc)[3], const int32_t *ccell,
-                                               const int8_t *ccls, const int32_t *ccq0,
-                                               const double (*cbox)[6], int tpf,
-                                               const uint16_t *bin, int cnt, bool from_end,
-                                               int cap, double *res) {
+                                               const GroupData &G, const uint16_t *bin, int cnt,
+                                               bool from_end, int cap) {
   const int lane = threadIdx.x;
   for (int t0 = 0; t0 < cnt; t0 += kFastBlock / 3) {
     const int t = t0 + lane / 3, term = lane - 3 * (lane / 3);
     const bool on = lane < (kFastBlock / 3) * 3 && t < cnt;
     int item = 0;
-    double val = 0.0, w = 0.0, det = 0.0;
+    double val = 0.0, vol = 0.0, ratio = 0.0;
     if (on) {
-      item = bin[from_end ? cap - 1 - t : t];
-      Tet T;
-      int cell, cl;
-      Pl p0, p1, p2, p3;
-      queued_pair(m, s, qpair, tets, fc, ccell, ccls, ccq0, cbox, tpf, item, T, det, cell, cl,
-                  p0, p1, p2, p3);
-      val = split_term<K>(dist_table<K>(T, p0, p1, p2, p3), term);
-      w = class_weight(s, cell, cl);
+      const TD<R> D = pair_table<R>(m, s, G, bin[from_end ? cap - 1 - t : t], item, vol, ratio);
+      val = split_term<R>(D, term);
     }
     const double v1 = __shfl_down(val, 1), v2 = __shfl_down(val, 2);
-    if (on && term == 0) res[item] = w * (det * ((val + v1) + v2));
+    if (on && term == 0) G.res[item] = vol * (ratio * ((val + v1) + v2));
   }
 }
 
-// A phase-B bin of pairs of K planes, one lane per pair (64 pairs per pass):
-// the whole recursion of the closed form in the pair's lane.
-template <int K>
-__device__ __forceinline__ void one_lane_bin(const DMesh &m, const DState &s,
-                                             const uint32_t *qpair,
-                                             const GroupTets &tets,
-                                             const double (*fc)[3], const int32_t *ccell,
-                                             const int8_t *ccls, const int32_t *ccq0,
-                                             const double (*cbox)[6], int tpf,
-                                             const uint16_t *bin, int cnt, bool from_end, int cap,
-                                             double *res) {
-  for (int t = (int)threadIdx.x; t < cnt; t += kFastBlock) {
-    const int item = bin[from_end ? cap - 1 - t : t];
-    Tet T;
-    int cell, cl;
-    double det;
-    Pl p0, p1, p2, p3;
-    queued_pair(m, s, qpair, tets, fc, ccell, ccls, ccq0, cbox, tpf, item, T, det, cell, cl, p0,
-                p1, p2, p3);
-    const double v = kept_fraction<K>(dist_table<K>(T, p0, p1, p2, p3));
-    res[item] = class_weight(s, cell, cl) * (det * v);
-  }
-}
-
-// A phase-B bin of pairs of five planes of cells that are not boxes, nine
-// lanes per pair (term j of piece i of the first two planes' splits; seven
-// pairs per pass), filled from the end of bin (capacity cap).  The terms are
-// combined as the recursion adds them: the three of a piece, then the pieces
-// weighted by their ratios.
-__device__ __forceinline__ void nine_lane_bin(const DMesh &m, const DState &s,
-                                              const uint32_t *qpair,
-                                              const GroupTets &tets,
-                                              const double (*fc)[3], const int32_t *ccell,
-                                              const int8_t *ccls, const int32_t *ccq0, int tpf,
-                                              const uint16_t *bin, int cnt, int cap,
-                                              double *res) {
+// A phase-B bin of pairs of five planes and no leading one (cells that are not
+// boxes), nine lanes per pair (term j of piece i of the first two planes'
+// splits; seven pairs per pass), filled from the end of bin (capacity cap).
+// The terms are combined as the recursion adds them: the three of a piece,
+// then the pieces weighted by their ratios.
+__device__ __forceinline__ void nine_lane_bin(const DMesh &m, const DState &s, const GroupData &G,
+                                              const uint16_t *bin, int cnt, int cap) {
   const int lane = threadIdx.x;
   for (int t0 = 0; t0 < cnt; t0 += kFastBlock / 9) {
     const int t = t0 + lane / 9, sub = lane - 9 * (lane / 9);
     const int i = sub / 3, j = sub - 3 * i;
     const bool on = lane < (kFastBlock / 9) * 9 && t < cnt;
     int item = 0;
-    double val = 0.0, ri = 0.0, w = 0.0, det = 0.0;
+    double val = 0.0, ri = 0.0, vol = 0.0;
     if (on) {
-      item = bin[cap - 1 - t];
-      const uint32_t qp = qpair[item];
-      const int l = pair_tet(qp), u = pair_cand(qp), lf = tet_face(l, tpf);
-      const int cell = ccell[u];
-      const v3 c = mk3(fc[lf][0], fc[lf][1], fc[lf][2]);
-      const Tet T = group_tet(tets, l);
-      det = tets.det[l];
-      const int cl = ccls[u] & 7;
+      item = bin[cap - 1 - t] & 1023;
+      const uint32_t qp = G.qpair[item];
+      const int l = pair_tet(qp), u = pair_cand(qp), lf = tet_face(l, G.tpf);
+      const int cell = G.ccell[u];
+      const v3 c = mk3(G.fc[lf][0], G.fc[lf][1], G.fc[lf][2]);
+      const Tet T = group_tet(G.tets, l);
+      const int cl = G.ccls[u] & 7;
+      vol = class_weight(s, cell, cl) * G.tets.det[l];
       // the four cutting planes in mask order, then the PLIC plane (or, of a
       // cell without one, the fifth cutting plane)
-      const int q0 = ccq0 ? ccq0[u] : m.cf_off[cell];
-      uint32_t mm = qp & 0xffffu;
+      const int q0 = G.ccq0[u];
+      uint32_t mm = pair_mask(qp);
       const Pl a = cell_plane_at(m, q0 + __builtin_ctz(mm), c);
       mm &= mm - 1;
       const Pl b = cell_plane_at(m, q0 + __builtin_ctz(mm), c);
@@ -1273,25 +1285,49 @@ __device__ __forceinline__ void nine_lane_bin(const DMesh &m, const DState &s,
       mm &= mm - 1;
       const Pl pl = mm ? cell_plane_at(m, q0 + __builtin_ctz(mm), c) : plic_plane_at(s, cell, c);
       val = split_term2<5>(dist_table<5>(T, a, b, d, e, pl), i, j, ri);
-      w = class_weight(s, cell, cl);
     }
     const double f = (val + __shfl_down(val, 1)) + __shfl_down(val, 2);
     const double ti = ri * f;
     const double tot = (ti + __shfl_down(ti, 3)) + __shfl_down(ti, 6);
-    if (on && sub == 0) res[item] = w * (det * tot);
+    if (on && sub == 0) G.res[item] = vol * tot;
   }
 }
 
-// Tests of one candidate cell against the tets of its face, bit by bit: E
-// holds the tets with a vertex strictly inside a bound or plane, N those with
-// a vertex strictly outside.
+// Tests of one candidate cell against the tets of its face, bit by bit: e
+// holds the tets with a vertex strictly inside a bound or plane, n1 and n2 the
+// low and high bit of the number of their vertices strictly outside (mod 4:
+// a tet with all four outside has no bit in e).
 struct SideBits {
-  uint32_t e, n;
+  uint32_t e, n1, n2;
 };
 __device__ __forceinline__ void side_bits(SideBits &b, double d, uint32_t tets) {
   b.e |= d > 0.0 ? tets : 0u;
-  b.n |= d < 0.0 ? tets : 0u;
+  const uint32_t x = d < 0.0 ? tets : 0u;
+  b.n2 ^= b.n1 & x;
+  b.n1 ^= x;
 }
+// the tets that the plane cuts, and those of them it keeps one vertex of
+__device__ __forceinline__ uint32_t cut_bits(const SideBits &b) { return b.n1 | b.n2; }
+__device__ __forceinline__ uint32_t corner_bits(const SideBits &b) { return b.n1 & b.n2; }
+
+// Two sets of a face's tets side by side: in one word where a face has at most
+// 15 (triangle faces), else in two.  The last bit of the second is a flag.
+struct TetSets32 {
+  uint32_t v;
+  __device__ __forceinline__ void set(uint32_t a, uint32_t b) { v = a | (b << 16); }
+  __device__ __forceinline__ uint32_t a(int k) const { return (v >> k) & 1u; }
+  __device__ __forceinline__ uint32_t b(int k) const { return (v >> (k + 16)) & 1u; }
+  static constexpr uint32_t kFlag = 1u << 15;
+  __device__ __forceinline__ uint32_t flag() const { return v & (1u << 31); }
+};
+struct TetSets64 {
+  uint2 v;
+  __device__ __forceinline__ void set(uint32_t a, uint32_t b) { v = make_uint2(a, b); }
+  __device__ __forceinline__ uint32_t a(int k) const { return (v.x >> k) & 1u; }
+  __device__ __forceinline__ uint32_t b(int k) const { return (v.y >> k) & 1u; }
+  static constexpr uint32_t kFlag = 1u << 31;
+  __device__ __forceinline__ uint32_t flag() const { return v.y & (1u << 31); }
+};
 
 // Which tets k (bits 0..) of a face may overlap a candidate cell, and for each
 // of the cell's planes j which of them it cuts, from the nv vertices of the
@@ -1304,8 +1340,9 @@ __device__ __forceinline__ void side_bits(SideBits &b, double d, uint32_t tets) 
 __device__ __forceinline__ uint32_t box_side_bits(double lo, double hi, double c, int a,
                                                   const double (*vx)[3],
                                                   const unsigned long long *vt, int nv, int kb,
-                                                  uint32_t all, uint32_t &cut0, uint32_t &cut1) {
-  SideBits up{0u, 0u}, dn{0u, 0u};
+                                                  uint32_t all, uint32_t &cut0, uint32_t &cut1,
+                                                  uint32_t &one0, uint32_t &one1) {
+  SideBits up{0u, 0u, 0u}, dn{0u, 0u, 0u};
   const double wu = hi - c, wd = c - lo;
   side_bits(up, wu, all);  // the apex
   side_bits(dn, wd, all);
@@ -1315,18 +1352,21 @@ __device__ __forceinline__ uint32_t box_side_bits(double lo, double hi, double c
     side_bits(up, wu - x, t);
     side_bits(dn, wd + x, t);
   }
-  cut0 = up.n & all;
-  cut1 = dn.n & all;
+  cut0 = cut_bits(up);
+  cut1 = cut_bits(dn);
+  one0 = corner_bits(up);
+  one1 = corner_bits(dn);
   return all & up.e & dn.e;
 }
 // A cell that is no box: its bounds and its planes, the first RP of which have
-// their cut tets in cut[]; planes beyond these only take tets off the result,
+// their cut tets in cut[] (and in one[] those they keep one vertex of); planes beyond these only take tets off the result,
 // and recut is set: the mask has to be found pair by pair.
 template <int RP>
 __device__ __forceinline__ uint32_t cand_tests(const DMesh &m, v3 lo, v3 hi, v3 c, int q0, int np,
                                                const double (*vx)[3],
                                                const unsigned long long *vt, int nv, int kb,
-                                               uint32_t all, uint32_t (&cut)[RP], bool &recut) {
+                                               uint32_t all, uint32_t (&cut)[RP],
+                                               uint32_t (&one)[RP], bool &recut) {
   recut = false;
   uint32_t lx = 0, ly = 0, lz = 0, hx = 0, hy = 0, hz = 0;
   auto bound = [&](v3 y, uint32_t t) {
@@ -1342,7 +1382,7 @@ __device__ __forceinline__ uint32_t cand_tests(const DMesh &m, v3 lo, v3 hi, v3 
 #pragma unroll
   for (int j = 0; j < RP; ++j) {
     pl[j] = j < np ? cell_plane_at(m, q0 + j, c) : Pl{0, 0, 0, 1.0};
-    b[j] = SideBits{0u, 0u};
+    b[j] = SideBits{0u, 0u, 0u};
     side_bits(b[j], pl[j].w, all);  // the apex
   }
   bound(c, all);
@@ -1357,13 +1397,14 @@ __device__ __forceinline__ uint32_t cand_tests(const DMesh &m, v3 lo, v3 hi, v3 
 #pragma unroll
   for (int j = 0; j < RP; ++j) {
     hit &= b[j].e;
-    cut[j] = b[j].n;
+    cut[j] = cut_bits(b[j]);
+    one[j] = corner_bits(b[j]);
   }
   if (np > RP) {
     recut = true;
     for (int j = RP; j < np; ++j) {
       const Pl q = cell_plane_at(m, q0 + j, c);
-      SideBits x{0u, 0u};
+      SideBits x{0u, 0u, 0u};
       side_bits(x, q.w, all);
       for (int v = 0; v < nv; ++v)
         side_bits(x, q.w - dot(mk3(q.x, q.y, q.z), mk3(vx[v][0], vx[v][1], vx[v][2])),
@@ -1396,12 +1437,16 @@ __device__ __forceinline__ unsigned long long bit_range(int lo, int hi) {
 // by at most one plane are summed at once (a single kept fraction), pairs of
 // two to MAXPL planes go to bins by plane count, and a tet with a pair of more
 // planes goes to the general kernel's queue.
-// Phase B evaluates each bin with the plane count uniform across the wave:
-// pairs of two planes one lane each (the whole recursion), of three planes one
-// lane each on tetrahedral meshes and three lanes each on hexahedral ones, of
-// four three lanes each (one per piece of the first plane's split), of five
-// nine lanes each (one per piece of the first two splits); phase C adds each
-// tet's pairs in stencil order.
+// Phase B evaluates each bin with the plane count uniform across the wave.  A
+// pair with a plane that keeps one vertex of its tet takes that plane first
+// and goes on as the corner it leaves, with a plane fewer (80 % of the pairs
+// of three and four planes on tetrahedra, 60 % on cubes; without, every pair
+// runs through all pieces of its first split, as some lane needs them).  Then
+// pairs of up to two planes one lane each (the whole recursion), of three
+// planes one lane each on tetrahedral meshes and three lanes each on
+// hexahedral ones, of four three lanes each (one per piece of the first
+// plane's split), of five nine lanes each (one per piece of the first two
+// splits); phase C adds each tet's pairs in stencil order.
 // Bound by issued FP64 and select instructions of phase B, with the lanes over
 // candidates, tets, pairs and pieces in turn so that none waits for the tet
 // with the most work (with a tet per lane through phase A, half of a step on
@@ -1417,11 +1462,12 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
                                                 unsigned long long &npairs,
                                                 unsigned long long &nresc) {
   static_assert(MAXPL <= 4 || !BOXES, "five-plane pairs only for cells that are not boxes");
-  static_assert(CAP >= 63 * TPL && CAP < 65536, "a round takes at least one lane's tets");
+  static_assert(CAP >= 63 * TPL && CAP <= 1024, "a round takes at least one lane's tets");
   static_assert(CAND <= 256 && TPL * kFastBlock <= 128, "fields of a queued pair");
   constexpr int kRP = BOXES ? 6 : 4;           // planes with cut bits in registers
   constexpr int kPer = BOXES ? 3 : 1;          // lanes per candidate in its tests (one per axis)
-  constexpr int kBatch = 5 * kSmallFace;       // tets per face whose bits fit a word
+  // tets per face whose bits fit a table's word
+  constexpr int kBatch = BOXES ? 5 * kSmallFace : 15;
   // stencil entries per lane whose ids and classes load together
   constexpr int kScan = BOXES ? 2 : 4;
   __shared__ double vtx[kVtxPool][3];
@@ -1432,10 +1478,11 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
   __shared__ double tdet[TPL * kFastBlock];
   __shared__ uint32_t qpair[CAP];
   __shared__ double res[CAP];
-  // pairs of two and more planes by plane count: two planes from the start of
-  // bins[0], five from its end, three from the start of bins[1] and four from
-  // its end (CAP pairs at most)
-  __shared__ uint16_t bins[2][CAP];
+  // pairs of two and more planes, by their planes beside a leading one: one
+  // from the start of bins[0], two from the start of bins[1], four from its
+  // end, three from the start of bins[2] and five from its end (CAP pairs at
+  // most)
+  __shared__ uint16_t bins[3][CAP];
   // candidates of face fi at fi * (CAND / F) + position
   __shared__ int32_t ccell[CAND];
   __shared__ int8_t ccls[CAND];  // class | 8 for a box cell
@@ -1446,9 +1493,12 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
   __shared__ double cbox[BOXES ? CAND : 1][6];
   __shared__ double fbox[kGroupFaces][6];
   __shared__ int cnum[kGroupFaces];
-  // phase A's tables, kept over the rounds
-  __shared__ uint2 whi[CAND];
-  __shared__ uint32_t wc[kRP * CAND];
+  // phase A's tables, kept over the rounds: the tets a candidate overlaps and
+  // those inside it (flag: masks to be found pair by pair), and those its plane
+  // j cuts and keeps one vertex of
+  using TetSets = typename std::conditional<BOXES, TetSets64, TetSets32>::type;
+  __shared__ TetSets whi[CAND];
+  __shared__ TetSets wc[kRP * CAND];
   __shared__ uint8_t tdef[TPL * kFastBlock];  // tets left to the general clip
   const int lane = threadIdx.x;
   const int F = gtets / tpf;       // faces per group, 1..kGroupFaces
@@ -1650,17 +1700,15 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
     int kb = 0, tested = -1;
     for (;;) {
       const int nb = tpf - kb < kBatch ? tpf - kb : kBatch;
-      // phase A, lanes over the candidates: tests into the tables whi (tets
-      // overlapped, and tets inside; bit 31 of these: masks to be found pair by
-      // pair) and wc (tets cut by plane j), once per batch
+      // phase A, lanes over the candidates: their tests, once per batch
       for (int j0 = 0; j0 < (tested == kb ? 0 : total); j0 += kFastBlock / kPer) {
         const int j = j0 + lane / kPer, part = kPer > 1 ? lane % kPer : 0;
         const bool on = j < total && lane < (kFastBlock / kPer) * kPer;
-        uint32_t e = 0u, n[kRP];
+        uint32_t e = 0u, n[kRP], one[kRP];
         int r = 0;
         bool box = false, recut = false;
 #pragma unroll
-        for (int q = 0; q < kRP; ++q) n[q] = 0u;
+        for (int q = 0; q < kRP; ++q) n[q] = one[q] = 0u;
         if (on) {
           int f = 0, at = 0;
 #pragma unroll
@@ -1682,18 +1730,19 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
               e = box_side_bits(part == 0 ? cbox[r][0] : (part == 1 ? cbox[r][1] : cbox[r][2]),
                                 part == 0 ? cbox[r][3] : (part == 1 ? cbox[r][4] : cbox[r][5]),
                                 part == 0 ? c.x : (part == 1 ? c.y : c.z), part, &vtx[f * nvf],
-                                &vtet[f * nvf], nvf, kb, all, n[0], n[1]);
+                                &vtet[f * nvf], nvf, kb, all, n[0], n[1], one[0],
+                                one[1]);
             } else if (part == 0) {
               const int cell = ccell[r];
               e = cand_tests<kRP>(m, mk3(cbox[r][0], cbox[r][1], cbox[r][2]),
                                   mk3(cbox[r][3], cbox[r][4], cbox[r][5]), c, m.cf_off[cell],
                                   m.npl[cell], &vtx[f * nvf], &vtet[f * nvf], nvf, kb, all, n,
-                                  recut);
+                                  one, recut);
             }
           } else {
             const int cell = ccell[r];
             e = cand_tests<kRP>(m, xyz(m.bblo[cell]), xyz(m.bbhi[cell]), c, ccq0[r], m.npl[cell],
-                                &vtx[f * nvf], &vtet[f * nvf], nvf, kb, all, n, recut);
+                                &vtx[f * nvf], &vtet[f * nvf], nvf, kb, all, n, one, recut);
           }
         }
         uint32_t any = 0u;
@@ -1706,16 +1755,16 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
           if (box) {
             e &= e1 & e2;
             any |= a1 | a2;
-            wc[2 * part * CAND + r] = n[0];
-            wc[(2 * part + 1) * CAND + r] = n[1];
+            wc[2 * part * CAND + r].set(n[0], one[0]);
+            wc[(2 * part + 1) * CAND + r].set(n[1], one[1]);
           }
         }
         if (on && part == 0) {
           if (!box) {
 #pragma unroll
-            for (int q = 0; q < kRP; ++q) wc[q * CAND + r] = n[q];
+            for (int q = 0; q < kRP; ++q) wc[q * CAND + r].set(n[q], one[q]);
           }
-          whi[r] = make_uint2(e, recut ? 1u << 31 : e & ~any);
+          whi[r].set(e, recut ? TetSets::kFlag : e & ~any);
         }
       }
       tested = kb;
@@ -1732,9 +1781,9 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
           const int nc = min(cnum[fi[i]] - skip, kc);
 #pragma unroll 4
           for (int ci = 0; ci < nc; ++ci) {
-            const uint2 b = whi[fi[i] * kc + ci];
-            hits[i] |= (unsigned long long)((b.x >> kt) & 1u) << ci;
-            ins[i] |= (unsigned long long)((b.y >> kt) & 1u) << ci;
+            const TetSets b = whi[fi[i] * kc + ci];
+            hits[i] |= (unsigned long long)b.a(kt) << ci;
+            ins[i] |= (unsigned long long)b.b(kt) << ci;
           }
           if (ins[i]) hits[i] &= ins[i] ^ (ins[i] - 1ull);
         }
@@ -1761,9 +1810,12 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
             const int u = fi[i] * kc + __builtin_ctzll(h);
             uint32_t mask = 0u;
 #pragma unroll
-            for (int q = 0; q < kRP; ++q) mask |= ((wc[q * CAND + u] >> kt) & 1u) << q;
+            for (int q = 0; q < kRP; ++q) {
+              const TetSets b = wc[q * CAND + u];
+              mask |= (b.a(kt) << q) | (b.b(kt) << (q + 8));
+            }
             qpair[at++] = mask | ((uint32_t)u << 16) |
-                          ((uint32_t)(lane + i * kFastBlock) << 24) | (whi[u].y & (1u << 31));
+                          ((uint32_t)(lane + i * kFastBlock) << 24) | whi[u].flag();
           }
         } else {
           mcnt[i] = 0;
@@ -1772,10 +1824,10 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
       __syncthreads();
       {
         // lanes over the pairs
-        int nbin[4] = {0, 0, 0, 0};
+        int nbin[5] = {0, 0, 0, 0, 0};
         for (int p0 = 0; p0 < cnt; p0 += kFastBlock) {
           const int item = p0 + lane;
-          int bin = -1;
+          int bin = -1, lead = 0;
           if (item < cnt) {
             uint32_t qp = qpair[item];
             const int l = pair_tet(qp), u = pair_cand(qp), lf = tet_face(l, tpf);
@@ -1783,7 +1835,7 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
             const bool box = BOXES && (ccls[u] & 8);
             const v3 c = mk3(fc[lf][0], fc[lf][1], fc[lf][2]);
             const Tet T = group_tet(tets, l);
-            uint32_t mask = qp & 0xffffu;
+            uint32_t mask = pair_mask(qp);
             bool plic = cl == 1;
             double val = 0.0;
             bool out = false;
@@ -1791,7 +1843,7 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
               v3 lo, hi;
               tet_bbox(c, T.b, T.c, T.d, lo, hi);
               out = pair_cuts(m, c, T, lo, hi, cell, mask) < 0;
-              qp = (qp & 0x7fff0000u) | mask;
+              qp = (qp & 0xffff0000u) | mask;
               qpair[item] = qp;
             }
             const int ncut = __builtin_popcount(mask);
@@ -1824,41 +1876,41 @@ __device__ __forceinline__ void clip_fast_group(const DMesh &m, const DState &s,
             } else if (npl > MAXPL) {
               tdef[l] = 1;
             } else {
-              bin = npl - 2;
+              const uint32_t ones = pair_corners(qp);
+              if (ones) lead = 1 + __builtin_ctz(ones);
+              else if (plic && (d.a >= 0.0) + (d.b >= 0.0) + (d.c >= 0.0) + (d.d >= 0.0) == 1)
+                lead = kLeadPlic;
+              bin = npl - 1 - (lead != 0);
             }
             res[item] = val;
           }
 #pragma unroll
-          for (int b = 0; b < MAXPL - 1; ++b) {
+          for (int b = 0; b < MAXPL; ++b) {
             const unsigned long long mb = __ballot(bin == b);
             if (bin == b) {
               int pos = nbin[b] + (int)__popcll(mb & lt);
-              if (b >= 2) pos = CAP - 1 - pos;
-              bins[b == 0 || b == 3 ? 0 : 1][pos] = (uint16_t)item;
+              if (b >= 3) pos = CAP - 1 - pos;
+              bins[b < 3 ? b : b - 2][pos] = (uint16_t)(item | (lead << 10));
             }
             nbin[b] += (int)__popcll(mb);
           }
         }
         __syncthreads();
         // phase B, one bin at a time (the plane count uniform across the wave):
-        // pairs of two planes one lane each, of three planes three lanes each
-        // (one each on tetrahedral meshes, whose bins are fuller), of four three
-        // lanes each.  Every bin takes the same way whatever its size: which
-        // faces share a group follows the order of the geometric-face list,
-        // which is not fixed from run to run.
-        const int32_t *q0s = BOXES ? nullptr : ccq0;
-        one_lane_bin<2>(m, s, qpair, tets, fc, ccell, ccls, q0s, cbox, tpf, bins[0], nbin[0],
-                        false, CAP, res);
+        // pairs of one and two planes one lane each, of three planes three lanes
+        // each (one each on tetrahedral meshes, whose bins are fuller), of four
+        // three lanes each, of five nine.  Every bin takes the same way whatever
+        // its size: which faces share a group follows the order of the
+        // geometric-face list, which is not fixed from run to run.
+        const GroupData G{tets, fc, ccell, ccls, BOXES ? nullptr : ccq0, cbox, qpair, res, tpf};
+        one_lane_bin<1>(m, s, G, bins[0], nbin[0]);
+        one_lane_bin<2>(m, s, G, bins[1], nbin[1]);
         if constexpr (BOXES)
-          three_lane_bin<3>(m, s, qpair, tets, fc, ccell, ccls, q0s, cbox, tpf, bins[1], nbin[1],
-                            false, CAP, res);
+          three_lane_bin<3>(m, s, G, bins[2], nbin[2], false, CAP);
         else
-          one_lane_bin<3>(m, s, qpair, tets, fc, ccell, ccls, q0s, cbox, tpf, bins[1], nbin[1],
-                          false, CAP, res);
-        three_lane_bin<4>(m, s, qpair, tets, fc, ccell, ccls, q0s, cbox, tpf, bins[1], nbin[2],
-                          true, CAP, res);
-        if constexpr (MAXPL >= 5)
-          nine_lane_bin(m, s, qpair, tets, fc, ccell, ccls, q0s, tpf, bins[0], nbin[3], CAP, res);
+          one_lane_bin<3>(m, s, G, bins[2], nbin[2]);
+        three_lane_bin<4>(m, s, G, bins[1], nbin[3], true, CAP);
+        if constexpr (MAXPL >= 5) nine_lane_bin(m, s, G, bins[2], nbin[4], CAP);
         __syncthreads();
         // phase C
         int from = mstart;
