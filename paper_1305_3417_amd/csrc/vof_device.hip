@@ -56,6 +56,7 @@ constexpr int kLedgerBlock = 1024;  // the one block of the ledger's second stag
 constexpr int kGenTets = 3;        // deferred tets per wavefront in the general clip
 constexpr int kGenLanes = 21;      // lanes per tet (a hex face's stencil is 18 cells)
 static_assert(kGenTets * kGenLanes <= 64, "tets of a wavefront");
+constexpr int kPolySlots = 8;      // polytopes of a wave in the general clip
 constexpr int kWispGrid = 2048;    // blocks of the wisp passes (wave-stride over the lists)
 
 __device__ __forceinline__ v3 xyz(double4 a) { return mk3(a.x, a.y, a.z); }
@@ -2017,13 +2018,20 @@ __device__ __forceinline__ void clip_general_tets(const DMesh &m, const DState &
                                                   const DParams &p, int i0, int count, double dt,
                                                   double sc, unsigned long long &ncap,
                                                   unsigned long long &npairs) {
-  __shared__ double lx[kPolyCap], ly[kPolyCap], lz[kPolyCap], ld[kPolyCap];
-  __shared__ uint8_t lnb[3 * kPolyCap], laux[kPolyCap];
+  // kPolySlots polytopes, so that the lanes that need one take turns in groups
+  // (a polytope is one chain of LDS accesses: lane after lane they took 160 us
+  // a step for the few such tets of sixteen meshes, in groups 77)
+  __shared__ double lx[kPolySlots][kPolyCap], ly[kPolySlots][kPolyCap], lz[kPolySlots][kPolyCap],
+      ld[kPolySlots][kPolyCap];
+  __shared__ uint8_t lnb[kPolySlots][3 * kPolyCap], laux[kPolySlots][kPolyCap];
   static_assert(kClipBlock == 64, "one wave per block");
   const int lane = threadIdx.x;
   Poly P;
-  P.px = lx; P.py = ly; P.pz = lz; P.ps = ld;
-  P.nb = lnb; P.aux = laux;
+  auto use_poly = [&](int slot) {
+    P.px = lx[slot]; P.py = ly[slot]; P.pz = lz[slot]; P.ps = ld[slot];
+    P.nb = lnb[slot]; P.aux = laux[slot];
+  };
+  use_poly(0);
   P.st = 1; P.cap = kPolyCap; P.nv = 0;
 
   __shared__ double red[2][kClipBlock];
@@ -2127,13 +2135,17 @@ __device__ __forceinline__ void clip_general_tets(const DMesh &m, const DState &
       const bool pend = act && v != v;
       unsigned long long pm = __ballot(pend);
       while (pm) {
-        const int L = __ffsll((long long)pm) - 1;
-        pm &= pm - 1ull;
-        // the polytope changes hands: order one lane's LDS traffic before
-        // the next lane's (without this the compiler may interleave them)
+        // the next kPolySlots lanes that need a polytope
+        const int rank = (int)__popcll(pm & ((1ull << lane) - 1ull));
+        const bool turn = ((pm >> lane) & 1ull) && rank < kPolySlots;
+        pm &= ~__ballot(turn);
+        // the polytopes change hands: order one group's LDS traffic before the
+        // next one's (without this the compiler may interleave them)
         __syncthreads();
-        if (lane == L)
+        if (turn) {
+          use_poly(rank);
           v = pair_phase6(m, s, p, c, T, det, lo, hi, m.st[e], P, ncap, npairs, &vc, true);
+        }
       }
       __syncthreads();
       a += v;
