@@ -338,7 +338,11 @@ __global__ void k_point_velocity(DMesh m, const double *U0c, double4 *U, double 
   int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (p >= m.np) return;
   v3 u = mk3(0, 0, 0);
-  for (int k = m.pc_off[p]; k < m.pc_off[p + 1]; ++k) {
+  // unrolled so that the cell ids and weights, then the velocities, load
+  // together
+  const int k1 = m.pc_off[p + 1];
+#pragma unroll 8
+  for (int k = m.pc_off[p]; k < k1; ++k) {
     int64_t c = m.pc[k];
     u = u + m.wpc[k] * mk3(U0c[3 * c], U0c[3 * c + 1], U0c[3 * c + 2]);
   }
