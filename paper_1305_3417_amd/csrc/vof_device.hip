@@ -361,6 +361,29 @@ __global__ void k_reset(DState s) {
   if (threadIdx.x < kWNum) s.work[threadIdx.x] = 0;
 }
 
+__global__ void k_begin(DState s, int n_steps) {
+  s.stepno[0] = 0;
+  s.stepno[1] = n_steps;
+}
+__global__ __launch_bounds__(kBlock) void k_reset_stats(DState s) {
+  const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
+  if (i < kCntWords) s.cnt[i] = 0ull;
+  if (i == 0) {
+    s.flags[0] = 0u;
+    s.ledger[0] = 0.0;
+  }
+}
+__global__ __launch_bounds__(kBlock) void k_split_planes(const double4 *plane, int64_t n,
+                                                         double *normal, double *pos) {
+  const int64_t c = blockIdx.x * (int64_t)kBlock + threadIdx.x;
+  if (c >= n) return;
+  const double4 p = plane[c];
+  normal[3 * c] = p.x;
+  normal[3 * c + 1] = p.y;
+  normal[3 * c + 2] = p.z;
+  pos[c] = p.w;
+}
+
 // kClassCells cells per thread, strided by the grid (coalesced), and the
 // thread's interface cells appended together: one atomic per block of
 // kBlock * kClassCells cells on the list's counter.
@@ -2934,6 +2957,17 @@ static void launch_reconstruct_impl(const DMesh &m, const DState &s, const DPara
   k_cell_class<<<grid_for(m.nc, kBlock * kClassCells), kBlock, 0, st>>>(m, s, p);
   k_point_prep<<<grid_for(m.np, kBlock), kBlock, 0, st>>>(m, s, p);
   launch_plane(m, s, p, st);
+}
+
+void launch_begin(const DState &s, int n_steps, hipStream_t st) {
+  k_begin<<<1, 1, 0, st>>>(s, n_steps);
+}
+void launch_reset_stats(const DState &s, hipStream_t st) {
+  k_reset_stats<<<grid_for(kCntWords, kBlock), kBlock, 0, st>>>(s);
+}
+void launch_split_planes(const double4 *plane, int64_t n, double *normal, double *pos,
+                         hipStream_t st) {
+  k_split_planes<<<grid_for(n, kBlock), kBlock, 0, st>>>(plane, n, normal, pos);
 }
 
 // A step starts from zero work counters (the previous step's last kernel

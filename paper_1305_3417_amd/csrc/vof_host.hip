@@ -507,6 +507,7 @@ vof_status vof_mesh_upload(vof_context *ctx, const vof_mesh_desc *d, vof_mesh **
   ALLOC(ds.stepno, 2); ALLOC(ds.work, kWNum); ALLOC(ds.cnt, kCntWords); ALLOC(ds.flags, 1); ALLOC(ds.ledger, 1);
   ALLOC(ds.part, (nc + 255) / 256 > 256 ? (nc + 255) / 256 : 256);
   ALLOC(m->stats_buf, 1); ALLOC(m->stats_part, 4 * kStatsBlocks);
+  ALLOC(m->stage, 4 * nc);
 #undef ALLOC
 #define UP(dst, src, n)                                                                    \
   do { if ((rc = to_device(dst, src, n, VOF_HOST, s))) { delete m; return rc; } } while (0)
@@ -727,19 +728,20 @@ vof_status vof_set_velocity(vof_mesh *m, const double *U0c, const double *F0, in
   vof_status rc = check_memory(memory);
   if (rc || (rc = set_device(m->ctx))) return rc;
   hipStream_t s = m->ctx->stream;
-  double *tmp = nullptr;
-  HIP_OR_FAIL(hipMalloc(&tmp, sizeof(double) * 3 * (size_t)m->dm.nc));
-  rc = to_device(tmp, U0c, 3 * m->dm.nc, memory, s);
-  if (!rc) rc = to_device(m->ds.F0, F0, m->dm.nf, memory, s);
-  if (!rc) {
-    launch_point_velocity(m->dm, tmp, m->ds.U, m->ds.XU, m->ds.coef, s);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) rc = fail(VOF_EDEVICE, "point velocity: %s", hipGetErrorString(e));
+  const hipMemcpyKind kind = memory == VOF_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice;
+  // the point kernels run while the fluxes are copied; one wait at the end
+  double *u0 = m->stage;
+  hipError_t e = hipMemcpyAsync(u0, U0c, sizeof(double) * 3 * (size_t)m->dm.nc, kind, s);
+  if (e == hipSuccess) {
+    launch_point_velocity(m->dm, u0, m->ds.U, m->ds.XU, m->ds.coef, s);
+    e = hipGetLastError();
   }
-  (void)hipFree(tmp);
-  if (!rc) m->have_velocity = true;
-  return rc;
+  if (e == hipSuccess) e = hipMemcpyAsync(m->ds.F0, F0, sizeof(double) * (size_t)m->dm.nf, kind, s);
+  const hipError_t done = hipStreamSynchronize(s);  // also after an error: the copies end here
+  if (e == hipSuccess) e = done;
+  if (e != hipSuccess) return fail(VOF_EDEVICE, "velocity: %s", hipGetErrorString(e));
+  m->have_velocity = true;
+  return VOF_OK;
 }
 
 vof_status vof_reconstruct(vof_mesh *m) {
@@ -764,19 +766,28 @@ vof_status vof_advect(vof_mesh *m, int32_t n_steps, const double *dt, const doub
   vof_status rc = set_device(m->ctx);
   if (rc) return rc;
   hipStream_t s = m->ctx->stream;
+  HIP_OR_FAIL(hipStreamSynchronize(s));
   if (n_steps > m->step_cap) {
-    HIP_OR_FAIL(hipStreamSynchronize(s));
-    if ((rc = m->alloc(&m->ds.dt, n_steps))) return rc;
-    if ((rc = m->alloc(&m->ds.sc, n_steps))) return rc;
+    double *sched = nullptr;
+    if ((rc = m->alloc(&sched, 2 * (int64_t)n_steps))) return rc;
+    m->ds.dt = sched;
+    m->ds.sc = sched + n_steps;
     m->step_cap = n_steps;
     m->graph_ok = false;
-  } else {
-    HIP_OR_FAIL(hipStreamSynchronize(s));
   }
-  HIP_OR_FAIL(hipMemcpy(m->ds.dt, dt, sizeof(double) * n_steps, hipMemcpyHostToDevice));
-  HIP_OR_FAIL(hipMemcpy(m->ds.sc, scale, sizeof(double) * n_steps, hipMemcpyHostToDevice));
-  const int32_t first[2] = {0, n_steps};
-  HIP_OR_FAIL(hipMemcpy(m->ds.stepno, first, sizeof first, hipMemcpyHostToDevice));
+  if (m->step_cap <= n_steps + 256) {
+    // dt, then scale from the array's middle on: one copy
+    std::vector<double> sched((size_t)(m->step_cap + n_steps), 1.0);
+    std::copy(dt, dt + n_steps, sched.begin());
+    std::copy(scale, scale + n_steps, sched.begin() + m->step_cap);
+    HIP_OR_FAIL(hipMemcpy(m->ds.dt, sched.data(), sizeof(double) * sched.size(),
+                          hipMemcpyHostToDevice));
+  } else {
+    HIP_OR_FAIL(hipMemcpy(m->ds.dt, dt, sizeof(double) * n_steps, hipMemcpyHostToDevice));
+    HIP_OR_FAIL(hipMemcpy(m->ds.sc, scale, sizeof(double) * n_steps, hipMemcpyHostToDevice));
+  }
+  launch_begin(m->ds, n_steps, s);
+  HIP_OR_FAIL(hipGetLastError());
   if (m->profiling) {
     // room for every kernel of every step; pairs are folded into totals by
     // vof_read_profile
@@ -871,20 +882,11 @@ vof_status vof_read_planes(vof_mesh *m, int8_t *cls, double *normal, double *sv,
   int64_t nc = m->dm.nc;
   if (cls && (rc = from_device(cls, m->ds.cls, nc, memory, s))) return rc;
   if (normal || sv) {
-    std::vector<double4> pl(nc);
-    if ((rc = from_device(pl.data(), m->ds.plane, nc, VOF_HOST, s))) return rc;
-    std::vector<double> nn(normal ? 3 * nc : 0), ss(sv ? nc : 0);
-    for (int64_t c = 0; c < nc; ++c) {
-      if (normal) { nn[3 * c] = pl[c].x; nn[3 * c + 1] = pl[c].y; nn[3 * c + 2] = pl[c].z; }
-      if (sv) ss[c] = pl[c].w;
-    }
-    if (normal && (rc = (memory == VOF_HOST)
-                            ? (std::memcpy(normal, nn.data(), sizeof(double) * 3 * nc), VOF_OK)
-                            : to_device(normal, nn.data(), 3 * nc, VOF_HOST, s)))
-      return rc;
-    if (sv && (rc = (memory == VOF_HOST) ? (std::memcpy(sv, ss.data(), sizeof(double) * nc), VOF_OK)
-                                          : to_device(sv, ss.data(), nc, VOF_HOST, s)))
-      return rc;
+    double *nn = m->stage, *ss = nn + 3 * nc;  // split on the device
+    launch_split_planes(m->ds.plane, nc, nn, ss, s);
+    HIP_OR_FAIL(hipGetLastError());
+    if (normal && (rc = from_device(normal, nn, 3 * nc, memory, s))) return rc;
+    if (sv && (rc = from_device(sv, ss, nc, memory, s))) return rc;
   }
   return VOF_OK;
 }
@@ -949,9 +951,8 @@ vof_status vof_reset_stats(vof_mesh *m) {
   vof_status rc = set_device(m->ctx);
   if (rc) return rc;
   hipStream_t s = m->ctx->stream;
-  HIP_OR_FAIL(hipMemsetAsync(m->ds.cnt, 0, sizeof(unsigned long long) * kCntWords, s));
-  HIP_OR_FAIL(hipMemsetAsync(m->ds.flags, 0, sizeof(uint32_t), s));
-  HIP_OR_FAIL(hipMemsetAsync(m->ds.ledger, 0, sizeof(double), s));
+  launch_reset_stats(m->ds, s);
+  HIP_OR_FAIL(hipGetLastError());
   HIP_OR_FAIL(hipStreamSynchronize(s));
   return VOF_OK;
 }

@@ -45,6 +45,7 @@ struct vof_mesh {
   bool have_alpha = false, have_velocity = false;
   vof::StatsOut *stats_buf = nullptr;
   double *stats_part = nullptr;  // 4 kStatsBlocks
+  double *stage = nullptr;       // 4 nc: cell velocities coming in, planes going out
   bool profiling = false;
   vof::Prof prof;
   // the launch sequence of one step captured once (valid while the kernel

@@ -241,6 +241,13 @@ struct Fork {
 };
 void launch_step(const DMesh &m, const DState &s, const DParams &p, hipStream_t st, Prof *prof,
                  const Fork *fork);
+// Before the first step of a call of n_steps.
+void launch_begin(const DState &s, int n_steps, hipStream_t st);
+// Counters, flags and ledger to zero.
+void launch_reset_stats(const DState &s, hipStream_t st);
+// Planes as packed normals (3 n) and positions (n).
+void launch_split_planes(const double4 *plane, int64_t n, double *normal, double *pos,
+                         hipStream_t st);
 void launch_reconstruct(const DMesh &m, const DState &s, const DParams &p, hipStream_t st);
 constexpr int kStatsBlocks = 1024;
 void launch_stats(const DMesh &m, const DState &s, double *part, StatsOut *out, hipStream_t st);
