@@ -436,7 +436,9 @@ double vof_selftest_tet_clip(const double *tet, int32_t n_planes, const double *
  * the kernels add them when three lanes share a pair (four-plane pairs, and
  * three-plane pairs on hexahedral meshes), and NaN when it differs from the
  * one-lane recursion (the other pairs) by more than 1e-14 of the
- * tetrahedron's volume. */
+ * tetrahedron's volume, or when taking a plane that keeps one vertex first
+ * does, also with a vertex that lies on that plane to rounding moved to its
+ * either side. */
 double vof_selftest_tet_clip_closed(const double *tet, int32_t n_planes, const double *planes);
 
 #ifdef __cplusplus

@@ -281,12 +281,14 @@ VHD double kept_fraction(TD<K> T) {
 // A plane that keeps exactly one vertex of T (its distances in d) leaves one
 // tetrahedron, so it is applied first where a pair has such a plane: D, the
 // distances to the other K planes, becomes that of the kept corner, and the
-// result is the corner's volume ratio.  (The parameters are clamped: the one
-// kept vertex may have been found with other rounding.)
+// result is the corner's volume ratio.  The corner is the vertex of the largest
+// distance and the parameters are clamped: that the plane keeps one vertex was
+// found by another evaluation of the distances, so a vertex on the plane to
+// rounding may have either sign here, and costs a rounding of the volume only.
 template <int K>
 VHD double corner_cut(D4 d, TD<K> &D) {
-  const bool kb = d.b >= 0.0, kc = d.c >= 0.0 && !kb, ke = d.d >= 0.0 && !kb && !kc;
-  const double a = kb ? d.b : (kc ? d.c : (ke ? d.d : d.a));
+  const double ab = dmax(d.a, d.b), abc = dmax(ab, d.c), a = dmax(abc, d.d);
+  const bool ke = d.d > abc, kc = d.c > ab && !ke, kb = d.b > d.a && !kc && !ke;
   const VD<K> A = sel(kb, D.b, sel(kc, D.c, sel(ke, D.e, D.a)));
   auto cut = [&](bool moved, const VD<K> &own, double down, double &r) {
     const VD<K> v = sel(moved, D.a, own);

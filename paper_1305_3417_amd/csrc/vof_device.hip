@@ -3164,28 +3164,40 @@ double host_tet_clip_closed(const double *tet, int n_planes, const double *plane
                            : split_term<4>(dist_table<4>(T, pl[0], pl[1], pl[2], pl[3]), i);
   const double three = det * ((t[0] + t[1]) + t[2]);
   if (!(fabs(three - one) <= 1e-14 * det)) return NAN;
-  // every plane that keeps one vertex, taken first as the pairs' leading plane
+  // every plane that keeps one vertex, taken first as the pairs' leading plane;
+  // again with each vertex that lies on the plane to rounding moved onto it and
+  // to its either side, as the kernel's two evaluations of a distance may differ
   for (int i = 0; i < n_planes; ++i) {
     const D4 d = plane_dists(T, pl[i]);
     if ((d.a >= 0.0) + (d.b >= 0.0) + (d.c >= 0.0) + (d.d >= 0.0) != 1) continue;
     Pl o[3] = {pl[0], pl[0], pl[0]};
     for (int j = 0, n = 0; j < n_planes; ++j)
       if (j != i) o[n++] = pl[j];
-    double f;
-    if (n_planes == 2) {
-      TD<1> D = dist_table<1>(T, o[0], o[1], o[2], o[2]);
-      const double r = corner_cut<1>(d, D);
-      f = r * kept_fraction<1>(D);
-    } else if (n_planes == 3) {
-      TD<2> D = dist_table<2>(T, o[0], o[1], o[2], o[2]);
-      const double r = corner_cut<2>(d, D);
-      f = r * kept_fraction<2>(D);
-    } else {
+    auto corner = [&](const D4 &dd) {
+      if (n_planes == 2) {
+        TD<1> D = dist_table<1>(T, o[0], o[1], o[2], o[2]);
+        const double r = corner_cut<1>(dd, D);
+        return r * kept_fraction<1>(D);
+      }
+      if (n_planes == 3) {
+        TD<2> D = dist_table<2>(T, o[0], o[1], o[2], o[2]);
+        const double r = corner_cut<2>(dd, D);
+        return r * kept_fraction<2>(D);
+      }
       TD<3> D = dist_table<3>(T, o[0], o[1], o[2], o[2]);
-      const double r = corner_cut<3>(d, D);
-      f = r * kept_fraction<3>(D);
+      const double r = corner_cut<3>(dd, D);
+      return r * kept_fraction<3>(D);
+    };
+    if (!(fabs(det * corner(d) - one) <= 1e-14 * det)) return NAN;
+    const double size = dmax(dmax(fabs(d.a), fabs(d.b)), dmax(fabs(d.c), fabs(d.d)));
+    const double v[4] = {d.a, d.b, d.c, d.d};
+    for (int q = 0; q < 4; ++q) {
+      if (!(fabs(v[q]) <= 1e-15 * size)) continue;
+      for (double x : {0.0, fabs(v[q]), -fabs(v[q])}) {
+        const D4 near{q == 0 ? x : d.a, q == 1 ? x : d.b, q == 2 ? x : d.c, q == 3 ? x : d.d};
+        if (!(fabs(det * corner(near) - one) <= 1e-14 * det)) return NAN;
+      }
     }
-    if (!(fabs(det * f - one) <= 1e-14 * det)) return NAN;
   }
   return three / 6.0;
 }
