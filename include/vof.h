@@ -271,7 +271,7 @@ typedef struct {
   int64_t general_tets;       /* flux tets clipped by the general polytope path */
   double ledger;              /* sum of V_{f,alpha} over boundary faces      */
   double mass;                /* sum_c V_c alpha_c (compensated)            */
-  double alpha_min, alpha_max;
+  double alpha_min, alpha_max; /* of the cells that hold numbers; NaN if none does */
   int64_t wisps;              /* sum over steps of wisps found (wisps = 1)   */
   int64_t wisps_left;         /* of those, wisps with too little room around */
   int64_t chunk_rescans;      /* face groups whose stencils were scanned again

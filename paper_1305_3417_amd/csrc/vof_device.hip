@@ -2496,6 +2496,11 @@ __global__ __launch_bounds__(kLedgerBlock) void k_ledger(DMesh m, DState s, DPar
 struct MassAcc {
   double sum, comp, mn, mx;  // sum + comp: the compensated sum
 };
+// Of no cells.  The range starts from NaN, which minimum and maximum pass over,
+// so it is that of the cells that hold numbers, and NaN where none does.
+__device__ __forceinline__ MassAcc mass_none() {
+  return MassAcc{0.0, 0.0, __builtin_nan(""), __builtin_nan("")};
+}
 // Sum of two compensated sums; the rounding of the addition goes to comp.
 __device__ __forceinline__ MassAcc mass_add(const MassAcc &a, const MassAcc &b) {
   const double t = a.sum + b.sum, z = t - a.sum;
@@ -2515,7 +2520,7 @@ __device__ MassAcc mass_block(MassAcc v) {
   return v;
 }
 __global__ __launch_bounds__(kBlock) void k_stats_cells(DMesh m, DState s, double *part) {
-  MassAcc v{0.0, 0.0, 1e300, -1e300};
+  MassAcc v = mass_none();
   const int64_t stride = (int64_t)gridDim.x * kBlock;
 #pragma unroll 4
   for (int64_t c = blockIdx.x * (int64_t)kBlock + threadIdx.x; c < m.nc; c += stride) {
@@ -2530,7 +2535,7 @@ __global__ __launch_bounds__(kBlock) void k_stats_cells(DMesh m, DState s, doubl
 }
 __global__ __launch_bounds__(kBlock) void k_stats_sum(DState s, const double *part, int n,
                                                       StatsOut *out) {
-  MassAcc v{0.0, 0.0, 1e300, -1e300};
+  MassAcc v = mass_none();
   for (int i = threadIdx.x; i < n; i += kBlock) {
     const double *p = part + 4 * (int64_t)i;
     v = mass_add(v, MassAcc{p[0], p[1], p[2], p[3]});
