@@ -768,19 +768,20 @@ vof_status vof_advect(vof_mesh *m, int32_t n_steps, const double *dt, const doub
   hipStream_t s = m->ctx->stream;
   HIP_OR_FAIL(hipStreamSynchronize(s));
   if (n_steps > m->step_cap) {
-    double *sched = nullptr;
-    if ((rc = m->alloc(&sched, 2 * (int64_t)n_steps))) return rc;
-    m->ds.dt = sched;
-    m->ds.sc = sched + n_steps;
+    double *both = nullptr;
+    if ((rc = m->alloc(&both, 2 * (int64_t)n_steps))) return rc;
+    m->ds.dt = both;
+    m->ds.sc = both + n_steps;
     m->step_cap = n_steps;
     m->graph_ok = false;
   }
-  if (m->step_cap <= n_steps + 256) {
-    // dt, then scale from the array's middle on: one copy
-    std::vector<double> sched((size_t)(m->step_cap + n_steps), 1.0);
-    std::copy(dt, dt + n_steps, sched.begin());
-    std::copy(scale, scale + n_steps, sched.begin() + m->step_cap);
-    HIP_OR_FAIL(hipMemcpy(m->ds.dt, sched.data(), sizeof(double) * sched.size(),
+  // dt, then scale from the array's middle on: one copy where both fit the
+  // stack (a copy costs about 10 us, some 60 us a step at the least), else two
+  double sched[1024];
+  if (m->step_cap + (int64_t)n_steps <= (int64_t)(sizeof sched / sizeof sched[0])) {
+    std::fill(std::copy(dt, dt + n_steps, sched), sched + m->step_cap, 1.0);
+    std::copy(scale, scale + n_steps, sched + m->step_cap);
+    HIP_OR_FAIL(hipMemcpy(m->ds.dt, sched, sizeof(double) * (m->step_cap + n_steps),
                           hipMemcpyHostToDevice));
   } else {
     HIP_OR_FAIL(hipMemcpy(m->ds.dt, dt, sizeof(double) * n_steps, hipMemcpyHostToDevice));

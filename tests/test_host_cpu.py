@@ -1,0 +1,77 @@
+"""The library's host code without a GPU, on a stand-in for the HIP runtime
+(fake_hip.cpp: device memory is host memory, kernels are noted and not run):
+what a call copies, launches and waits for, and what it does where a copy or a
+host allocation fails.  Each test runs in a process of its own, with the
+stand-in loaded before the library."""
+from __future__ import annotations
+
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes as C, sys
+import numpy as np
+fake = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+fake.fake_fail_new.argtypes = [C.c_size_t]
+fake.fake_fail_copy.argtypes = [C.c_long]
+fake.fake_log_stop.restype = C.c_char_p
+import paper_1305_3417_amd as vof
+import workloads as W
+
+def logged(fn):
+    fake.fake_log_start()
+    try:
+        fn()
+    finally:
+        lines = fake.fake_log_stop().decode().splitlines()
+    out = []
+    for ln in lines:
+        what, a, b = ln.rsplit(" ", 2)
+        out.append((what, int(a), int(b)))
+    return out
+
+def upload(w):
+    m = vof.upload_mesh(ctx, w.mesh)
+    vof.vof_set_alpha(m, w.alpha0)
+    vof.vof_set_velocity(m, w.U0c, w.F0)
+    return m
+
+ctx = vof.vof_context_create(0, stream=0)
+"""
+
+
+@pytest.fixture(scope="module")
+def fake_hip(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake_hip") / "libfake_hip.so")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-w",
+                           "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-o", so,
+                           os.path.join(HERE, "fake_hip.cpp")])
+    return so
+
+
+def run(fake_hip, body):
+    r = subprocess.run([sys.executable, "-c", PRELUDE + textwrap.dedent(body), fake_hip],
+                       cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
+
+
+def test_schedules_need_no_host_memory(fake_hip):
+    """vof_advect stages the schedule without a host allocation of its size:
+    calls of one to many steps, before and after longer ones, pass where every
+    allocation of 1 KiB or more fails, and copy dt and scale."""
+    run(fake_hip, """
+    w = W.deform3d(4, steps=5000)
+    m = upload(w)
+    fake.fake_fail_new(1024)
+    for n in (1, 200, 2, 511, 512, 513, 3, 1100, 700, 5000, 1):
+        got = logged(lambda: vof.vof_advect(m, w.dt[:n], w.scale[:n]))
+        assert sum(g[0] == "graph" for g in got) == n
+        assert sum(g[2] for g in got if g[0] == "to_device") >= 16 * n
+    """)
