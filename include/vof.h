@@ -190,7 +190,9 @@ vof_status vof_map_alpha(vof_mesh *dst, vof_mesh *src, const int32_t *map_offset
  * free, eq. 2.4).  Step n of vof_advect uses scale[n] * U0c and
  * scale[n] * F0.  The point velocities U0_p are interpolated here by inverse
  * distance weighting (eqs. 2.6-2.7), and each face's flux-polyhedron volume
- * cubic for a unit sweep (Section 2.3) is computed once. */
+ * cubic for a unit sweep (Section 2.3) is computed once.  After VOF_EDEVICE
+ * the earlier velocity stands, or the mesh has none (steps are refused with
+ * VOF_EINVAL until a call passes). */
 vof_status vof_set_velocity(vof_mesh *mesh, const double *U0c, const double *F0,
                             int32_t memory);
 

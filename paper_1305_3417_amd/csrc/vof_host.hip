@@ -729,14 +729,33 @@ vof_status vof_set_velocity(vof_mesh *m, const double *U0c, const double *F0, in
   if (rc || (rc = set_device(m->ctx))) return rc;
   hipStream_t s = m->ctx->stream;
   const hipMemcpyKind kind = memory == VOF_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice;
-  // the point kernels run while the fluxes are copied; one wait at the end
   double *u0 = m->stage;
-  hipError_t e = hipMemcpyAsync(u0, U0c, sizeof(double) * 3 * (size_t)m->dm.nc, kind, s);
-  if (e == hipSuccess) {
+  auto points = [&] {
     launch_point_velocity(m->dm, u0, m->ds.U, m->ds.XU, m->ds.coef, s);
-    e = hipGetLastError();
+    return hipGetLastError();
+  };
+  auto fluxes = [&] {
+    return hipMemcpyAsync(m->ds.F0, F0, sizeof(double) * (size_t)m->dm.nf, kind, s);
+  };
+  hipError_t e = hipMemcpyAsync(u0, U0c, sizeof(double) * 3 * (size_t)m->dm.nc, kind, s);
+  if (memory == VOF_HOST) {
+    // the point kernels run while the fluxes are copied (90^3 cells: 1.10
+    // ms a call, 1.15 with the copies first); where only the first part passes,
+    // the mesh has no velocity until the next call
+    if (e == hipSuccess) {
+      m->have_velocity = false;
+      e = points();
+      if (e == hipSuccess) e = fluxes();
+    }
+  } else {
+    // device arrays: a copy that is refused (no device pointer) leaves the
+    // velocity as it was
+    if (e == hipSuccess) e = fluxes();
+    if (e == hipSuccess) {
+      m->have_velocity = false;
+      e = points();
+    }
   }
-  if (e == hipSuccess) e = hipMemcpyAsync(m->ds.F0, F0, sizeof(double) * (size_t)m->dm.nf, kind, s);
   const hipError_t done = hipStreamSynchronize(s);  // also after an error: the copies end here
   if (e == hipSuccess) e = done;
   if (e != hipSuccess) return fail(VOF_EDEVICE, "velocity: %s", hipGetErrorString(e));

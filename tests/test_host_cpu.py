@@ -75,3 +75,31 @@ def test_schedules_need_no_host_memory(fake_hip):
         assert sum(g[0] == "graph" for g in got) == n
         assert sum(g[2] for g in got if g[0] == "to_device") >= 16 * n
     """)
+
+
+@pytest.mark.parametrize("memory", ["host", "device"])
+def test_failed_velocity_is_not_used(fake_hip, memory):
+    """Where a copy of vof_set_velocity fails, no later step runs on a mixture
+    of two fields: either nothing was launched, so that the earlier velocity
+    still stands, or the mesh has no velocity.  Of device arrays the earlier
+    velocity always stands."""
+    run(fake_hip, f"\n    memory = {int(memory == 'device')}" + """
+    w = W.deform3d(4, steps=1)
+    def set_velocity(m):
+        U, F = 2.0 * w.U0c, 2.0 * w.F0
+        return vof.lib().vof_set_velocity(m.h, U.ctypes.data, F.ctypes.data, memory)
+    def kernels(got):
+        return [g for g in got if g[0].startswith("kernel")]
+    def stands(m):
+        return vof.lib().vof_advect(m.h, 1, w.dt.ctypes.data, w.scale.ctypes.data) == vof.VOF_OK
+    for nth in (1, 2):
+        m = upload(w)
+        assert len(kernels(logged(lambda: set_velocity(m)))) > 0 and stands(m)
+        fake.fake_fail_copy(nth)
+        codes = []
+        got = kernels(logged(lambda: codes.append(set_velocity(m))))
+        assert codes == [vof.VOF_EDEVICE]
+        assert stands(m) == (got == []), nth
+        assert got == [] or not memory
+        assert set_velocity(m) == vof.VOF_OK and stands(m)
+    """)
