@@ -12,6 +12,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -138,6 +139,12 @@ vof_status check_memory(int32_t memory) {
 }
 
 vof_status device_status(vof_mesh *m) { return vof::flags_status(m->ds.flags); }
+
+// Cells up to which planes for host arrays are copied whole and split on the
+// host: one copy, against a kernel and a copy per array, each of about 20 us
+// whatever its size.  (216 cells: 45 us, with the kernel 67; 21952: 61, 71;
+// 32768: 105, 84 - the host's pass over them takes over.)
+constexpr int64_t kPlanesOnHost = 24 * 1024;
 
 vof_params default_params() {
   vof_params p;
@@ -901,13 +908,27 @@ vof_status vof_read_planes(vof_mesh *m, int8_t *cls, double *normal, double *sv,
   hipStream_t s = m->ctx->stream;
   int64_t nc = m->dm.nc;
   if (cls && (rc = from_device(cls, m->ds.cls, nc, memory, s))) return rc;
-  if (normal || sv) {
-    double *nn = m->stage, *ss = nn + 3 * nc;  // split on the device
-    launch_split_planes(m->ds.plane, nc, nn, ss, s);
-    HIP_OR_FAIL(hipGetLastError());
-    if (normal && (rc = from_device(normal, nn, 3 * nc, memory, s))) return rc;
-    if (sv && (rc = from_device(sv, ss, nc, memory, s))) return rc;
+  if (!normal && !sv) return VOF_OK;
+  if (memory == VOF_HOST && nc <= kPlanesOnHost) {
+    std::unique_ptr<double4[]> pl(new (std::nothrow) double4[(size_t)nc]);
+    if (pl) {
+      if ((rc = from_device(pl.get(), m->ds.plane, nc, memory, s))) return rc;
+      for (int64_t c = 0; c < nc; ++c) {
+        if (normal) {
+          normal[3 * c] = pl[c].x;
+          normal[3 * c + 1] = pl[c].y;
+          normal[3 * c + 2] = pl[c].z;
+        }
+        if (sv) sv[c] = pl[c].w;
+      }
+      return VOF_OK;
+    }
   }
+  double *nn = m->stage, *ss = nn + 3 * nc;  // split on the device
+  launch_split_planes(m->ds.plane, nc, nn, ss, s);
+  HIP_OR_FAIL(hipGetLastError());
+  if (normal && (rc = from_device(normal, nn, 3 * nc, memory, s))) return rc;
+  if (sv && (rc = from_device(sv, ss, nc, memory, s))) return rc;
   return VOF_OK;
 }
 

@@ -103,3 +103,22 @@ def test_failed_velocity_is_not_used(fake_hip, memory):
         assert got == [] or not memory
         assert set_velocity(m) == vof.VOF_OK and stands(m)
     """)
+
+
+def test_planes_of_small_meshes_in_one_copy(fake_hip):
+    """vof_read_planes of a mesh of up to 24576 cells for host arrays: one copy
+    of the classes, one of the planes and no kernel, whichever arrays are
+    asked for; of more cells a kernel splits the planes first."""
+    run(fake_hip, """
+    for n, kernels, copies in ((4, 0, 2), (28, 0, 2), (30, 1, 3)):
+        w = W.deform3d(n, steps=1)
+        m = vof.upload_mesh(ctx, w.mesh)
+        vof.vof_set_alpha(m, w.alpha0)
+        got = logged(lambda: vof.vof_read_planes(m))
+        assert sum(g[0].startswith("kernel") for g in got) == kernels, n
+        assert sum(g[0] == "to_host" for g in got) == copies, n
+        s = np.empty(w.mesh.n_cells)
+        fake.fake_fail_new(1024)  # also where the host has no room for a copy
+        assert vof.lib().vof_read_planes(m.h, None, None, s.ctypes.data, 0) == vof.VOF_OK
+        fake.fake_fail_new(0)
+    """)
