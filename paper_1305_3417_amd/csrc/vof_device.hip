@@ -3045,8 +3045,8 @@ void launch_batch_begin(const BTab &t, int n, int n_steps, hipStream_t st) {
 // (the flux and register-clip kernels once per face kind present).
 void launch_batch_step(const BTab &t, const BConf &c, unsigned kinds, int ledger_grid,
                        hipStream_t st, const Fork *fork, hipEvent_t *ev) {
-  // ev (eager launches only): 0 start, 1 after the cell and point kernels, 2 after
-  // the plane kernel, 3 after the flux kernels, 4 after the register clips,
+  // ev (eager launches only, the plane kernel then in line): 0 start, 1 after the
+  // cell and point kernels, 2 after the plane kernel, 3 after the flux kernels, 4 after the register clips,
   // 5 before the update, 6 after the update, 7 after the ledger
   auto mark = [&](int i) {
     if (ev) (void)hipEventRecord(ev[i], st);
@@ -3083,8 +3083,9 @@ void launch_batch_step(const BTab &t, const BConf &c, unsigned kinds, int ledger
   // others.  (Jobs on hexahedra and tetrahedra of 12 to 32 cells a side: 157 and
   // 45 us a step one after the other, the run 11.6 -> 10.6 ms; sixteen uniform
   // and refined meshes 8.5 -> 7.8.)
+  // Timed steps too: the clip's grid and claim are chosen for both at once.
   unsigned aside = 0u;  // the kind's bit
-  if (fork && !ev) aside = (kinds & 1u) && (kinds & 6u) ? 1u : ((kinds & 6u) == 6u ? 2u : 0u);
+  if (fork) aside = (kinds & 1u) && (kinds & 6u) ? 1u : ((kinds & 6u) == 6u ? 2u : 0u);
   const bool both = aside != 0u;
   auto on = [&](unsigned kind) { return aside == kind ? fork->side : st; };
   if (both) {

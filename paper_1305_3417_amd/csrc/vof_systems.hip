@@ -175,11 +175,16 @@ struct BatchCore {
     return VOF_OK;
   }
 
-  vof_status capture(unsigned mask) {
-    if (!cap_stream) HIP_OR_FAIL(hipStreamCreateWithFlags(&cap_stream, hipStreamNonBlocking));
+  vof_status make_fork() {
     if (!fork.side) HIP_OR_FAIL(hipStreamCreateWithFlags(&fork.side, hipStreamNonBlocking));
     if (!fork.fork) HIP_OR_FAIL(hipEventCreateWithFlags(&fork.fork, hipEventDisableTiming));
     if (!fork.join) HIP_OR_FAIL(hipEventCreateWithFlags(&fork.join, hipEventDisableTiming));
+    return VOF_OK;
+  }
+
+  vof_status capture(unsigned mask) {
+    if (!cap_stream) HIP_OR_FAIL(hipStreamCreateWithFlags(&cap_stream, hipStreamNonBlocking));
+    if (vof_status rc = make_fork()) return rc;
     if (graph[mask]) {
       HIP_OR_FAIL(hipGraphExecDestroy(graph[mask]));
       graph[mask] = nullptr;
@@ -225,7 +230,8 @@ struct BatchCore {
   // one step launched kernel by kernel (no graph), e.g. to time a configuration
   vof_status step_eager(const BConf &c, hipEvent_t *ev) {
     if (n == 0) return VOF_OK;
-    launch_batch_step(tab, c, kinds, kMaxBatch, stream, nullptr, ev);
+    if (vof_status rc = make_fork()) return rc;
+    launch_batch_step(tab, c, kinds, kMaxBatch, stream, &fork, ev);
     HIP_OR_FAIL(hipGetLastError());
     return VOF_OK;
   }

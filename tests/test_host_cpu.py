@@ -122,3 +122,30 @@ def test_planes_of_small_meshes_in_one_copy(fake_hip):
         assert vof.lib().vof_read_planes(m.h, None, None, s.ctypes.data, 0) == vof.VOF_OK
         fake.fake_fail_new(0)
     """)
+
+
+def test_autotuner_times_the_step_that_runs(fake_hip):
+    """The autotuner's timed steps launch the clips of two and three face kinds
+    side by side as the captured step does: the same kernels on the same
+    number of streams, between the same fork and join."""
+    run(fake_hip, """
+    kinds = {"tets": W.rotate_tets(3, steps=4, sample=2), "hex": W.deform3d(4, steps=4),
+             "refined": W.deform3d_refined(4, steps=4)}
+    for names in (["hex"], ["tets", "hex"], ["hex", "refined"], ["tets", "hex", "refined"]):
+        ms = [upload(kinds[k]) for k in names]
+        b = vof.vof_batch_create(ctx, ms)
+        dt = np.stack([kinds[k].dt[:4] for k in names])
+        sc = np.stack([kinds[k].scale[:4] for k in names])
+        clips = {}
+        for what, fn in (("timed", vof.vof_autotune), ("run", vof.vof_batch_advect)):
+            got = logged(lambda: fn(b, dt, sc))
+            c = [g for g in got if "kb_clip_fast" in g[0]]
+            if what == "timed":
+                assert len(c) == 4 * len(names)
+                c = c[:len(names)]
+            main = next(g[1] for g in got if "kb_group_prefix" in g[0])
+            clips[what] = [(g[0], g[1] != main) for g in c]
+        assert clips["timed"] == clips["run"], names
+        assert sum(aside for _, aside in clips["run"]) == (len(names) > 1)
+        vof.vof_batch_destroy(b)
+    """)
