@@ -1,11 +1,13 @@
 """The register clip's face groups and claims.
 
 A face's phase volume does not depend on the group it is clipped in: a small
-mesh alone takes groups of one tet per lane, in a batch beside a mesh with
-many geometric faces groups of two, with other chunk and round boundaries, and
-its alpha and V_alpha are bitwise the same.  Nor on the claims: grids below
-and off the eight XCDs, and claims of one and of several groups, visit every
-group once.  Faces of three, four and up to eight points."""
+hexahedral mesh alone takes groups of one tet per lane, in a batch beside a
+mesh with many geometric faces groups of two, with other chunk and round
+boundaries, and its alpha and V_alpha are bitwise the same.  Nor on the claims:
+grids below and off the eight XCDs, and claims of one and of several groups,
+visit every group once.  Faces of three, four and up to eight points (the
+tets per lane go by the faces of a mesh's own kind, so the refined and the
+tetrahedral mesh keep one here and vary the claims only)."""
 from __future__ import annotations
 
 import numpy as np
