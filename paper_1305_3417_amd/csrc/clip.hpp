@@ -174,65 +174,10 @@ VHD Pl plane_rel(double4 pp, v3 c) {
 }
 VHD Pl plic_plane_at(const DState &s, int cell, v3 c) { return plane_rel(s.plane[cell], c); }
 
-// The planes bounding the phase region of a classified pair in slots
-// p0..p3: the cutting cell planes in mask order, then the PLIC plane of an
-// interface cell (slots past the last plane are left unspecified).
-VHD void pair_regs_q(const DMesh &m, const DState &s, v3 c, int cell, int cl, int q0,
-                     uint32_t mask, Pl &p0, Pl &p1, Pl &p2, Pl &p3) {
-  const Pl pl = cl == 1 ? plic_plane_at(s, cell, c) : Pl{0, 0, 0, 0};
-  uint32_t mm = mask;
-  p0 = mm ? cell_plane_at(m, q0 + __builtin_ctz(mm), c) : pl;
-  mm &= mm - 1;
-  p1 = mm ? cell_plane_at(m, q0 + __builtin_ctz(mm), c) : pl;
-  mm &= mm - 1;
-  p2 = mm ? cell_plane_at(m, q0 + __builtin_ctz(mm), c) : pl;
-  mm &= mm - 1;
-  p3 = mm ? cell_plane_at(m, q0 + __builtin_ctz(mm), c) : pl;
-}
-VHD void pair_regs(const DMesh &m, const DState &s, v3 c, int cell, int cl, uint32_t mask, Pl &p0,
-                   Pl &p1, Pl &p2, Pl &p3) {
-  pair_regs_q(m, s, c, cell, cl, m.cf_off[cell], mask, p0, p1, p2, p3);
-}
-
 // weight of a covered volume in the phase region of a full (2) or
 // vanishing-gradient (3) cell; interface cells carry it in their plane
 VHD double class_weight(const DState &s, int cell, int cl) {
   return cl == 3 ? s.alpha[cell] : 1.0;
-}
-
-// Register-only phase volume of flux tet k of face f (serial over the
-// stencil): every overlapping stencil cell contributes |T ∩ C ∩ H| through
-// at most kRegPlanes planes.  Returns false ("deferred") when a pair needs
-// more.
-VHD bool flux_tet_phase_fast(const DMesh &m, const DState &s, double dt, double sc, int f,
-                             int k, double &vol, unsigned long long &npairs) {
-  vol = 0.0;
-  v3 c, t1, t2, t3;
-  double det, sgn;
-  if (!flux_tet(m, s, dt, sc, f, k, c, t1, t2, t3, det, sgn)) return true;
-  const Tet T{mk3(0, 0, 0), t1, t2, t3};
-  v3 lo, hi;
-  tet_bbox(c, t1, t2, t3, lo, hi);
-  double acc = 0.0;
-  unsigned long long np = 0;
-  for (int e = m.st_off[f]; e < m.st_off[f + 1]; ++e) {
-    const int cell = m.st[e];
-    const int cl = s.cls[cell];
-    if (cl == 0) continue;
-    uint32_t mask;
-    const int ncut = pair_cuts(m, c, T, lo, hi, cell, mask);
-    if (ncut < 0) continue;
-    const int npl = ncut + (cl == 1);
-    if (npl > kRegPlanes) return false;
-    ++np;
-    Pl p0, p1, p2, p3;
-    pair_regs(m, s, c, cell, cl, mask, p0, p1, p2, p3);
-    acc += class_weight(s, cell, cl) * vol6_planes(T, det, p0, p1, p2, p3, npl);
-    if (ncut == 0) break;  // the tet lies inside this cell
-  }
-  npairs += np;
-  vol = sgn * acc / 6.0;
-  return true;
 }
 
 // Six times the phase volume of the positively ordered flux tet T (apex at
@@ -403,34 +348,6 @@ VHD double pair_phase6(const DMesh &m, const DState &s, const DParams &p, v3 c, 
   else if (cl == 3) vph = s.alpha[cell] * vc;
   if (p.check_stencil) *vcell = vc;
   return vph;
-}
-
-// Serial form over the whole stencil (host builds): the signed phase volume
-// of flux tet k of face f; with check_stencil, *deficit receives the signed
-// volume of the tet that no stencil cell covers and *gross its unsigned
-// volume.
-VHD double flux_tet_phase(const DMesh &m, const DState &s, const DParams &p, double dt,
-                          double sc, int f, int k, Poly &P, unsigned long long &ncap,
-                          unsigned long long &npairs, double *deficit, double *gross) {
-  *deficit = 0.0;
-  *gross = 0.0;
-  v3 c, t1, t2, t3;
-  double det, sgn;
-  if (!flux_tet(m, s, dt, sc, f, k, c, t1, t2, t3, det, sgn)) return 0.0;
-  const Tet T{mk3(0, 0, 0), t1, t2, t3};
-  v3 lo, hi;
-  tet_bbox(c, t1, t2, t3, lo, hi);
-  double acc = 0.0, cover = 0.0;
-  for (int e = m.st_off[f]; e < m.st_off[f + 1]; ++e) {
-    double vc;
-    acc += pair_phase6(m, s, p, c, T, det, lo, hi, m.st[e], P, ncap, npairs, &vc);
-    cover += vc;
-  }
-  if (p.check_stencil) {
-    *deficit = sgn * (det - cover) / 6.0;
-    *gross = det / 6.0;
-  }
-  return sgn * acc / 6.0;
 }
 
 }  // namespace vof

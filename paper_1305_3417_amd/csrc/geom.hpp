@@ -116,9 +116,6 @@ VHD double tet_kept_fraction(D4 d) {
   // all kept, none kept (the quotient above is then not used)
   return e >= 0.0 ? 1.0 : (a >= 0.0 ? f : 0.0);
 }
-VHD double tet_kept_fraction(const double dd[4]) {
-  return tet_kept_fraction(D4{dd[0], dd[1], dd[2], dd[3]});
-}
 
 // ---------------------------------------------------------------------------
 // register-only clipping of a tetrahedron by a few planes

@@ -456,14 +456,6 @@ __device__ __forceinline__ double wave_sum_d(double v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   return v;
 }
-__device__ __forceinline__ double wave_min_d(double v) {
-  for (int o = 32; o > 0; o >>= 1) v = dmin(v, __shfl_xor(v, o));
-  return v;
-}
-__device__ __forceinline__ double wave_max_d(double v) {
-  for (int o = 32; o > 0; o >>= 1) v = dmax(v, __shfl_xor(v, o));
-  return v;
-}
 
 // One tetrahedron (o, c_f, p_i, p_i+1) of the outward face fans of a cell,
 // relative to the cell centroid o, with its signed volume times six; empty
