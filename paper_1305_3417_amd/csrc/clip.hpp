@@ -1,5 +1,6 @@
-// clip.hpp -- phase volume of one tetrahedron of a flux polyhedron (step 5),
-// shared by the clip kernel and host builds of it.
+// clip.hpp -- phase volume of one tetrahedron of a flux polyhedron (step 5):
+// the tetrahedra, the classification of (tetrahedron, cell) pairs and the
+// general evaluation of a pair.
 //
 // Tetrahedron k of the flux polyhedron of face f at its corrected lam, apex at
 // the face centre (local origin):
@@ -8,10 +9,10 @@
 //   k = 5 i + 2         (m_i, p_i, q_i)
 //   k = 5 i + 3         (m_i, q_i, q_i+1)
 //   k = 5 i + 4         (m_i, q_i+1, p_i+1)
-// Returns its signed volume times the fraction lying in the phase region:
-// sum over stencil cells of |T ∩ C_c ∩ H_c| (eqs. 2.22-2.23), H = the PLIC
-// half-space in interface cells, all space in full cells, alpha-weighted in
-// vanishing-gradient cells, nothing in empty cells.
+// Its phase volume is its orientation times the sum over the stencil cells of
+// |T ∩ C_c ∩ H_c| (eqs. 2.22-2.23), H = the PLIC half-space in interface cells,
+// all space in full cells, alpha-weighted in vanishing-gradient cells, nothing
+// in empty cells.
 #pragma once
 
 #include "geom.hpp"
@@ -39,9 +40,6 @@ VHD void tet_bbox(v3 c, v3 t1, v3 t2, v3 t3, v3 &lo, v3 &hi) {
            dmax(dmax(0.0, t1.z), dmax(t2.z, t3.z))) + c;
 }
 
-// With check_stencil set, *deficit receives the signed volume of the tet that
-// no stencil cell covers (summed over a face it must vanish unless the flux
-// polyhedron leaves its stencil) and *gross its unsigned volume.
 // Vertices of tetrahedron k of face f's flux polyhedron at its corrected lam,
 // relative to the face centre c (the apex is the origin), positively ordered;
 // sgn is the orientation of the tet in the signed decomposition.  Returns
@@ -180,13 +178,6 @@ VHD double class_weight(const DState &s, int cell, int cl) {
   return cl == 3 ? s.alpha[cell] : 1.0;
 }
 
-// Six times the phase volume of the positively ordered flux tet T (apex at
-// the origin = face centre c, vol6 = det) inside stencil cell `cell`, with
-// (lo, hi) the tet's bounding box in mesh coordinates.  At most three planes
-// (cutting cell planes, plus the PLIC plane of an interface cell) take the
-// closed forms; more go through the vertex-graph polytope P (only when
-// poly_ok; otherwise such a pair returns NaN and is left untouched).  With
-// check_stencil, *vcell receives six times |T ∩ C| (the coverage), else 0.
 // A pair of four planes handed back: its six-fold phase volume is
 // w * det * f4(D), D the 4 x 4 vertex distances written to row[16] (vertex by
 // vertex, plane by plane) and f4 the kept fraction of four planes.  With
@@ -221,6 +212,15 @@ VHD void dists5(const Tet &T, Pl p0, Pl p1, Pl p2, Pl p3, Pl p4, double *row) {
   }
 }
 
+// Six times the phase volume of the positively ordered flux tet T (apex at
+// the origin = face centre c, vol6 = det) inside stencil cell `cell`, with
+// (lo, hi) the tet's bounding box in mesh coordinates.  At most kRegPlanes
+// planes (cutting cell planes, plus the PLIC plane of an interface cell) take
+// the closed forms; more go through the vertex-graph polytope P (only when
+// poly_ok; otherwise such a pair returns NaN and is left untouched).  With
+// check_stencil, *vcell receives six times |T ∩ C| (the coverage; over a face
+// the volume not covered must vanish unless the polyhedron leaves its
+// stencil), else 0.
 VHD double pair_phase6(const DMesh &m, const DState &s, const DParams &p, v3 c, const Tet &T,
                        double det, v3 lo, v3 hi, int cell, Poly &P, unsigned long long &ncap,
                        unsigned long long &npairs, double *vcell, bool poly_ok = true,

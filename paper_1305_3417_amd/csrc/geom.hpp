@@ -45,9 +45,10 @@ VHD double dmin(double a, double b) { return __builtin_fmin(a, b); }
 VHD double dmax(double a, double b) { return __builtin_fmax(a, b); }
 
 // n / d for |d| of 1e-300 to 1e290: a reciprocal refined twice and one residual
-// step of the quotient.  Eight instructions against about thirteen of the IEEE
-// division, which also scales operands that the clip never has; largest error
-// 0.5000 ulp over 1e8 random quotients, that of a correctly rounded division.
+// step of the quotient, which leave a rounding of it.  Eight instructions
+// against about thirteen of the IEEE division, which also scales operands
+// beyond that range; a product of four distances meets its lower end at a
+// length unit of about 1e-75 (and underflows at 1e-77).
 VHD double quot(double n, double d) {
 #if defined(__HIP_DEVICE_COMPILE__)
   double r = __builtin_amdgcn_rcp(d);
@@ -92,8 +93,9 @@ VHD v3 sel(bool c, v3 a, v3 b) {
 // instructions; only the order of kept before removed matters) and the case is
 // chosen by selects, without a branch, so every lane performs a single
 // division and neighbouring evaluations overlap.  The clip is bound by issued
-// instructions, most of them in this function and split_first: a step on 80^3
-// x 6 tetrahedra went from 2.26 to 1.91 ms, on 128^3 cubes from 0.412 to 0.400.
+// instructions, most of them in this function and split_first: in its form of
+// one tet per lane through all phases, a step on 80^3 x 6 tetrahedra went from
+// 2.26 to 1.91 ms, on 128^3 cubes from 0.412 to 0.400.
 VHD double tet_kept_fraction(D4 d) {
   const double x0 = dmax(d.a, d.b), x1 = dmin(d.a, d.b);
   const double y0 = dmax(d.c, d.d), y1 = dmin(d.c, d.d);

@@ -40,7 +40,7 @@ constexpr int kFastBlock = 64;   // one wave per block in the register clip
 // them).  Quad faces (a hex face's stencil: 18 cells, of which two or three
 // overlap the face's flux polyhedron) take the first, triangle faces of
 // tetrahedral meshes (58 stencil cells, about 7 overlapping cells per flux
-// tet) the second, at two to three waves per SIMD.
+// tet) the second.  Both run at two waves per SIMD.
 constexpr int kBoxTets = 2, kBoxCap = 304, kBoxCand = 72;
 constexpr int kTriTets = 1, kTriCap = 608, kTriCand = 192;
 constexpr int kFastPlanes = 4;   // planes per pair in the register clip (more: general)
@@ -96,8 +96,7 @@ __device__ __forceinline__ int64_t geo_slot(const DMesh &m, int na, int i) {
 }
 // Register-clip face groups of one mesh: the small faces' groups first
 // (tsmall tets per face), then the large faces' (the mesh's 5 * maxn), `tets`
-// tets per group at most.  The list counts are read once: the step's claim
-// counter shares their line.
+// tets per group at most.
 struct ClipGroups {
   int na, nb, tsmall, nsmall, total;
 };
@@ -1339,8 +1338,9 @@ struct TetSets64 {
 // tests of box_cuts (box cells) and pair_cuts_box, which need only the sign of
 // each vertex's distance, so they are made once per vertex and plane instead
 // of once per tet.  `all`: the face's tets.
-// The two planes of axis a of a box cell: + at hi and - at lo, c the axis
-// coordinate of the tets' apex.
+//
+// box_side_bits takes one axis a of a box cell: its planes + at hi and - at lo,
+// c the axis coordinate of the tets' apex.
 __device__ __forceinline__ uint32_t box_side_bits(double lo, double hi, double c, int a,
                                                   const double (*vx)[3],
                                                   const unsigned long long *vt, int nv, int kb,
@@ -1362,9 +1362,10 @@ __device__ __forceinline__ uint32_t box_side_bits(double lo, double hi, double c
   one1 = corner_bits(dn);
   return all & up.e & dn.e;
 }
-// A cell that is no box: its bounds and its planes, the first RP of which have
-// their cut tets in cut[] (and in one[] those they keep one vertex of); planes beyond these only take tets off the result,
-// and recut is set: the mask has to be found pair by pair.
+// cand_tests takes a cell that is no box: its bounds and its planes, the first
+// RP of which have their cut tets in cut[] (and in one[] those they keep one
+// vertex of); planes beyond these only take tets off the result, and recut is
+// set: the mask has to be found pair by pair.
 template <int RP>
 __device__ __forceinline__ uint32_t cand_tests(const DMesh &m, v3 lo, v3 hi, v3 c, int q0, int np,
                                                const double (*vx)[3],
@@ -1455,7 +1456,8 @@ __device__ __forceinline__ unsigned long long bit_range(int lo, int hi) {
 // candidates, tets, pairs and pieces in turn so that none waits for the tet
 // with the most work (with a tet per lane through phase A, half of a step on
 // tetrahedra went to lanes waiting): 24^3 x 6 tetrahedra 0.48 -> 0.29 ms a
-// step, 80^3 x 6 1.91 -> 1.45, 97 x 103 x 89 cubes 0.374 -> 0.360.
+// step, 80^3 x 6 1.91 -> 1.45, 97 x 103 x 89 cubes 0.374 -> 0.360; with the
+// leading planes and the joined gathers since then 0.22, 1.15 and 0.33.
 // Group g of one list of geometric faces of one mesh (`count` faces at gfaces
 // slots first, first + dir, ...; tpf tets per face, F = gtets / tpf per group),
 // swept by `sweep` (-s dt).  Must be reached by the whole wave.
@@ -2751,11 +2753,10 @@ void kb_flux(BTab t, int kind) {
   }
 }
 
-// Face groups of the geometric faces of the meshes of one face kind, claimed
-// `claim` at a time (the first by block index, the rest from a counter).
 // Prefix of the face groups of the register clip over the meshes of each
-// face kind (one block; after the flux kernels): kept in global memory, as
-// the clip kernel's LDS is what bounds its occupancy.
+// face kind, and the kind's tets per group (one block; after the flux kernels):
+// kept in global memory, as a copy in each clip block's LDS would cost
+// occupancy.
 __global__ __launch_bounds__(kBlock) void kb_group_prefix(BTab t) {
   __shared__ int32_t pre[kMaxBatch + 1];
   for (int kind = 0; kind < kFaceKinds; ++kind) {
@@ -2785,6 +2786,8 @@ __global__ __launch_bounds__(kBlock) void kb_group_prefix(BTab t) {
   }
 }
 
+// Step 5 on the register path over the groups of all meshes of one face kind,
+// claimed as in k_clip_fast, up to `most` at a time.
 template <int TPL, int CAP, int CAND, bool BOXES, int MAXPL>
 __global__ __launch_bounds__(kFastBlock) __attribute__((amdgpu_waves_per_eu(2)))
 void kb_clip_fast(BTab t, int kind, int most) {
