@@ -83,18 +83,26 @@ def _profile_record(prefix, tag):
     return rec if rec.get("source_sha256_16") == kernel_source_hash() else None
 
 
-def recorded_traffic(kernel):
+def recorded_traffic(kernel, unit=None, n_units=0.0):
     """HBM bytes per launch of `kernel` from the committed FETCH_SIZE / WRITE_SIZE
     summary of the profiled window (copy-calibrated), or None when it was taken
-    on other kernel sources."""
+    on other kernel sources.  With the kernel's unit of work (a key of the
+    window's counts), the bytes of a launch over `n_units` of them."""
     rec = _profile_record("hbm_traffic", "traffic-json")
-    return None if rec is None else rec["bytes_per_launch"].get(KERNEL_FUNCS.get(kernel, ""))
+    if rec is None:
+        return None
+    b = rec["bytes_per_launch"].get(KERNEL_FUNCS.get(kernel, ""))
+    if b is None or unit is None:
+        return b
+    work = _profile_record("fp64_counters", "flops-json")
+    n = work and work.get("window_units_per_step", {}).get(unit)
+    return b * n_units / n if n else None
 
 
 def recorded_flops(kernel, unit):
-    """(executed FP64 flops per unit, VALU wave instructions per launch) of
-    `kernel` from the committed counter summary of the profiled window, or
-    None when it was taken on other kernel sources."""
+    """(executed FP64 flops, VALU wave instructions) of `kernel` per unit of its
+    work from the committed counter summary of the profiled window, or None when
+    it was taken on other kernel sources."""
     rec = _profile_record("fp64_counters", "flops-json")
     if rec is None or not rec.get("window_units_per_step"):
         return None
@@ -102,7 +110,8 @@ def recorded_flops(kernel, unit):
     n = rec["window_units_per_step"].get(unit)
     if f not in rec["flops_per_launch"] or not n:
         return None
-    return rec["flops_per_launch"][f] / n, rec.get("valu_insts_per_launch", {}).get(f)
+    insts = rec.get("valu_insts_per_launch", {}).get(f)
+    return rec["flops_per_launch"][f] / n, insts / n if insts else None
 
 
 CPU_SAMPLE_SECONDS = 10.0   # oracle steps are run until this much host time has passed
@@ -737,20 +746,22 @@ def main():
     if dom in units:
         n_units, estimate, what, key = units[dom]
         measured = recorded_flops(dom, key)
-        # executed FP64 flops counted on the same window (rocprofv3 FP64
-        # instruction counters x active lanes) when taken on these sources,
-        # else the per-unit estimate
+        # executed FP64 flops, instructions and bytes per unit as counted in the
+        # middle of the whole run (rocprofv3 counters x active lanes) when taken
+        # on these sources, else the per-unit estimate of the flops; this run's
+        # window may be another one, so all are scaled by its units
         per_unit = measured[0] if measured else estimate
         achieved = n_units * per_unit / avg_s / 1e12
         at_estimate = n_units * estimate / avg_s / 1e12
         roof.update({"achieved": achieved, "frac": achieved / PEAK_FP64_TFLOPS,
+                     "traffic": recorded_traffic(dom, key, n_units),
                      "units_per_launch": n_units, "flop_per_unit": per_unit,
                      "flop_per_unit_source": "rocprofv3 FP64 counters" if measured
                      else "estimate", "flop_per_unit_estimate": estimate,
                      "achieved_at_estimate": at_estimate,
                      "frac_at_estimate": at_estimate / PEAK_FP64_TFLOPS, "unit_kind": what})
         if measured and measured[1]:
-            issue = measured[1] / avg_s
+            issue = n_units * measured[1] / avg_s
             roof["valu_issue"] = {"wave_insts_per_s": issue, "peak": PEAK_VALU_WAVE_INSTS,
                                   "frac": issue / PEAK_VALU_WAVE_INSTS}
     step_after = mid + P
