@@ -4,7 +4,7 @@ the rounded face centre, as the cells' planes are taken against that centre.  A
 point on a cell's side then has the distance 0 and cuts nothing; with the
 subtraction fused into the centre's last product it lies a rounding off the
 side wherever the mean over three, five or more points is rounded, and the clip
-evaluates pairs that only touch (0.7 % more on these meshes).
+evaluates pairs that only touch (1 % more on these meshes).
 
 Every cell holds 0.37, so every face with flux is clipped; the velocity is
 uniform and oblique, so no tet is flat and only face points meet sides."""
